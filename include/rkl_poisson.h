@@ -76,7 +76,7 @@ typedef struct {
 /* V-cycle relaxation.  RKL_SMOOTH_RKL: one s-stage RKL tau-step per
  * relaxation (App. A eq. RKL_intermediate_source).  RKL_SMOOTH_GSRB: one
  * red-black Gauss-Seidel pass per relaxation, the paper's own smoother
- * (Sec. 2.2.4); the coarsest level is always solved by accelerated RKL. */
+ * (Sec. 2.2.4); the coarsest level is solved as coarse_tol says. */
 typedef enum { RKL_SMOOTH_RKL = 0, RKL_SMOOTH_GSRB = 1 } rkl_smoother;
 
 /* Solver options.  rkl_default_opts() fills the defaults noted here. */
@@ -93,7 +93,9 @@ typedef struct {
     int prec;            /* rkl_precision (default RKL_FP64)                                    */
     double four_pi_G;    /* f = four_pi_G * rho (default 4 pi, i.e. G = 1)                      */
     double coarse_tol;   /* coarsest solve: stop at ||M u - b|| <= coarse_tol ||b||; 0 picks
-                            1e-13 (float64) or 1e-6 (float32)                                   */
+                            1e-13 (float64) or 1e-6 (float32), which V-cycles then reach by a
+                            direct solve of the coarsest system (fast diagonalisation) when the
+                            accelerated RKL steps would reach it within coarse_max_steps         */
     int coarse_max_steps;/* coarsest solve: cap on tau-steps (default 200)                      */
     int smoother;        /* rkl_smoother: relaxation of the V-cycle above the coarsest level    */
                          /* (default RKL_SMOOTH_RKL)                                            */
@@ -248,9 +250,9 @@ rkl_status rkl_coarse_solve_f32(const rkl_grid *grid, const rkl_opts *opts, cons
  * members drop out while the others continue.  The refinement loop
  * (float64 defect, V-cycle on the correction at the working precision,
  * float64 update) is captured once into a HIP graph and replayed until every
- * member has stopped.  A class whose hierarchy does not end in the
- * one-workgroup coarse tail is solved member by member with the single-solve
- * path.  Returns the first non-OK member status in class order (each member's
+ * member has stopped.  A class whose hierarchy ends neither in the
+ * one-workgroup coarse tail nor in a direct coarsest solve is solved member by
+ * member with the single-solve path.  Returns the first non-OK member status in class order (each member's
  * own outcome is in stats[i]); phi of periodic members is mean-free.  Calls
  * on one process are serialised.  Buffers persist until rkl_release_all.
  */

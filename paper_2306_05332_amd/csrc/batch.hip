@@ -31,6 +31,7 @@ struct ClassPlan {
   int s = 2;             // stages per tau-step of this class
   int part_stride = 0;
   double *f0 = nullptr, *phi = nullptr, *res0sq = nullptr, *dsum = nullptr, *part = nullptr;
+  double* dirw = nullptr;  // scratch of the multi-workgroup direct coarsest solve
   double** tab_in = nullptr;
   double** tab_out = nullptr;
   ConvState* conv = nullptr;
@@ -87,6 +88,7 @@ ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
   C->res0sq = C->alloc<double>(nb);
   C->dsum = C->alloc<double>(2 * (size_t)nb);
   C->part = C->alloc<double>((size_t)nb * ps);
+  if (base.dirw != nullptr) C->dirw = C->alloc<double>((size_t)nb * base.lv[L - 1].n);
   C->tab_in = C->alloc<double*>(nb);
   C->tab_out = C->alloc<double*>(nb);
   C->conv = C->alloc<ConvState>(nb);
@@ -135,7 +137,7 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   } else {
     launch_fill<T>(cur, F.n, (T)0, stop, st, b0);
   }
-  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, VBatch{nb, CONV_INTS, ps, C.dsum, C.part});
+  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, VBatch{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw});
   launch_add_cast<T>(C.phi, cur, F.n, stop, st, Batch{nb, (long long)F.n, (long long)F.n, CONV_INTS, 0});
   check_launch();
 }
@@ -162,7 +164,7 @@ void class_iteration_direct(ClassPlan& C, const rkl_opts& o, hipStream_t st, int
   launch_check(C.part, nblk, 1, C.res0sq, o.tol, o.max_cycles, 1.0, C.conv, st, Batch{nb, 0, 0, 0, ps});
   check_launch();
   vcycle_from<double>(P, H, cur, alt, C.f0, nullptr, pair0 ? 2 : 1, o, stop, st,
-                      VBatch{nb, CONV_INTS, ps, C.dsum, C.part});
+                      VBatch{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw});
   for (int k = 0; k < 3; ++k)
     if (bufs[k] == cur) ia = k;
 }
@@ -322,6 +324,7 @@ hipGraphExec_t batch_graph(std::vector<ClassPlan*>& cls, const rkl_opts& o, int 
   for (auto* c : cls) sig.cls.push_back({c, iters});
   if (g_graph && g_graph->sig == sig) return g_graph->exec;
   tail_prepare();
+  direct_prepare();
   auto G = std::make_unique<GraphCache>();
   G->sig = sig;
   HIPCHK(hipStreamCreateWithFlags(&G->stream, hipStreamNonBlocking));
@@ -353,14 +356,21 @@ hipGraphExec_t batch_graph(std::vector<ClassPlan*>& cls, const rkl_opts& o, int 
   return g_graph->exec;
 }
 
-// A class runs batched when its hierarchy ends in the one-workgroup tail and
-// every level above the tail takes the fused tau-step.
+// A class runs batched when its hierarchy ends in the one-workgroup tail or
+// in the direct coarsest solve and every level above takes the fused tau-step.
+// Hierarchies without the tail of the accelerated iteration (coarsest levels
+// of more than 256 cells) run batched only up to CLASS_MAX_CELLS level-0 cells
+// in the class, whose arrays are then at most a few GB; larger ones are solved
+// member by member, within one member's arrays.
+constexpr size_t CLASS_MAX_CELLS = (size_t)1 << 26;
 template <typename T>
-bool class_ok(Plan& P, const rkl_opts& o) {
-  const int lt = tail_level<T>(P);
-  if (P.L() < 2 || lt <= 0) return false;
+bool class_ok(Plan& P, const rkl_opts& o, size_t nb) {
+  const bool direct = direct_coarse<T>(P, o);
+  const int lt = tail_level<T>(P, direct);
+  if (P.L() < 2 || (lt <= 0 && !direct)) return false;
+  if (tail_level<T>(P, false) <= 0 && nb * P.lv[0].n > CLASS_MAX_CELLS) return false;
   const int sf = o.smoother == RKL_SMOOTH_GSRB ? 2 : o.s;
-  for (int l = 0; l < lt; ++l)
+  for (int l = 0; l < (lt > 0 ? lt : P.L() - 1); ++l)
     if (!fused_tau_supported<T>(view<T>(P.lv[l], P.periodic, nullptr), sf)) return false;
   return true;
 }
@@ -380,7 +390,8 @@ rkl_status solve_batched(const rkl_grid* grids, int nbatch, const rkl_opts& o, c
     const rkl_grid& g = grids[kv.second[0]];
     const rkl_opts og = with_s(o, g);
     Plan& P = get_plan(g, og.s, og.tau_frac, og.min_coarse, og.prec);
-    const bool ok = og.prec == RKL_MIXED ? class_ok<float>(P, og) : class_ok<double>(P, og);
+    const bool ok = og.prec == RKL_MIXED ? class_ok<float>(P, og, kv.second.size())
+                                         : class_ok<double>(P, og, kv.second.size());
     if (!ok) {
       single.insert(single.end(), kv.second.begin(), kv.second.end());
       continue;

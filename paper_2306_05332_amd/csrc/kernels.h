@@ -272,6 +272,22 @@ void tune_clear();
 int tune_generation();
 const char* fused_variant_name(int variant);
 
+// Direct solve of the coarsest level (direct.h, direct.hip): the axes'
+// orthonormal eigenvectors and eigenvalues, `tab` (device) holding the rows of
+// Qx, Qy and Qz (nx^2 + ny^2 + nz^2 values), then the nx + ny + nz eigenvalues.
+struct DirectTables {
+  int nx, ny, nz;
+  const double* tab;
+};
+constexpr int DIRECT_LDS_CELLS = 2048;  // larger levels take the multi-workgroup form
+bool direct_axes_ok(int nx, int ny, int nz);
+void direct_prepare();
+// M u = b (homogeneous ghosts, or periodic: the constant mode is dropped); W:
+// scratch of nx ny nz doubles per member
+template <typename T>
+void launch_direct(const DirectTables& D, const T* b, T* u, double* W, const int* stop, hipStream_t st,
+                   const Batch& bt = single_batch());
+
 // Coarse tail of the V-cycle in one workgroup (tail.hip).
 constexpr int TAIL_MAX_LEVELS = 6;
 constexpr int TAIL_MAX_S = 8;
@@ -282,15 +298,18 @@ struct TailShape {
   int nx[TAIL_MAX_LEVELS], ny[TAIL_MAX_LEVELS], nz[TAIL_MAX_LEVELS];
   double ihx2[TAIL_MAX_LEVELS], ihy2[TAIL_MAX_LEVELS], ihz2[TAIL_MAX_LEVELS];
 };
+// direct: the coarsest level is solved directly (then the tail may consist of
+// that level alone)
 template <typename T>
-bool tail_fits(const TailShape& ts, int s);
+bool tail_fits(const TailShape& ts, int s, bool direct);
 // b_top: restricted right-hand side of the top tail level (mean not yet
 // removed); u_top receives that level's correction.  smooth[l]: the s stage
-// coefficients of tail level l.
+// coefficients of tail level l.  dir: tables of the direct coarsest solve, or
+// nullptr for the accelerated RKL iteration (cs, ctol, cmax).
 void tail_prepare();
 template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
-                 hipStream_t st, const Batch& bt = single_batch(), int gs = 0);
+                 hipStream_t st, const Batch& bt = single_batch(), int gs = 0, const DirectTables* dir = nullptr);
 
 }  // namespace rkl

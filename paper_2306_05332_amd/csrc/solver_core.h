@@ -92,6 +92,14 @@ struct Plan {
   int* d_coff = nullptr;
   double* d_coef = nullptr;
   int tail64 = -1, tail32 = -1;  // first level run by the one-workgroup tail (-1: none)
+  // direct coarsest solve (tab nullptr: not available on this hierarchy), the
+  // tail's first level with it, the scratch of its multi-workgroup form and
+  // the tau-steps in which the accelerated iteration surely reaches the default
+  // tolerance of either precision (0: not within 200)
+  DirectTables direct{0, 0, 0, nullptr};
+  int dtail64 = -1, dtail32 = -1;
+  double* dirw = nullptr;
+  int steps64 = 0, steps32 = 0;
   std::vector<void*> allocs;
   std::mutex mu;
 
@@ -449,8 +457,19 @@ void coarse_solve(Plan& P, Hier<T>& H, int l, const rkl_opts& o, const int* stop
 // On entry cur0 holds the iterate after `pre_done` level-0 relaxations
 // (alt0 is its alternate buffer); on exit cur0 holds the cycle's result.
 // faces0: level-0 Dirichlet data (float64 path only) or nullptr.
+// Whether the coarsest level is solved directly: the caller left the
+// tolerance at its default and the iteration would reach it within the step
+// cap, so both give the solution to that tolerance or better.  A tolerance or
+// a cap of the caller's own runs the accelerated RKL iteration as asked.
 template <typename T>
-int tail_level(const Plan& P) {
+bool direct_coarse(const Plan& P, const rkl_opts& o) {
+  const int steps = sizeof(T) == 8 ? P.steps64 : P.steps32;
+  return P.direct.tab != nullptr && o.coarse_tol == 0.0 && steps > 0 && steps <= o.coarse_max_steps;
+}
+
+template <typename T>
+int tail_level(const Plan& P, bool direct) {
+  if (direct) return sizeof(T) == 8 ? P.dtail64 : P.dtail32;
   return sizeof(T) == 8 ? P.tail64 : P.tail32;
 }
 
@@ -463,6 +482,7 @@ struct VBatch {
   int part_stride = 0;
   double* dsum = nullptr;
   double* part = nullptr;  // nullptr: the plan's own buffer
+  double* dirw = nullptr;  // direct coarsest solve's scratch (nullptr: the plan's own)
 };
 
 template <typename T>
@@ -483,8 +503,10 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
     return;
   }
   // levels lt.. run in the one-workgroup tail when they fit
-  const int lt = tail_level<T>(P);
-  if (vb.nb > 1 && lt <= 0) fail(RKL_EINVAL, "batched solves need the one-workgroup coarse tail");
+  const bool direct = direct_coarse<T>(P, o);
+  const int lt = tail_level<T>(P, direct);
+  if (vb.nb > 1 && lt <= 0 && !direct)
+    fail(RKL_EINVAL, "batched solves need the one-workgroup coarse tail or the direct coarsest solve");
   const int lbot = lt > 0 ? lt : L - 1;
   const bool fuse_rs = (o.fuse & 2) != 0;
   // pairs of partial sums the fused restriction into the next level wrote (0: restrict separately)
@@ -507,7 +529,8 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
       const StageCoef* sm[TAIL_MAX_LEVELS];
       for (int k = 0; k < ts.nlev; ++k) sm[k] = P.lv[lt + k].smooth.data();
       launch_tail<T>(ts, sm, o.s, o.n_pre, o.n_post, P.periodic ? 1 : 0, P.cs(), coarse_tol_for<T>(o),
-                     o.coarse_max_steps, H.b[lt], H.u[lt], stop, st, B1(lt), gs ? 1 : 0);
+                     o.coarse_max_steps, H.b[lt], H.u[lt], stop, st, B1(lt), gs ? 1 : 0,
+                     direct ? &P.direct : nullptr);
       check_launch();
       break;
     }
@@ -524,6 +547,9 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
       } else {
         launch_fill<T>(H.u[l], C.n, (T)0, stop, st, B1(l));
       }
+    } else if (direct) {
+      launch_direct<T>(P.direct, H.b[l], H.u[l], vb.dirw ? vb.dirw : P.dirw, stop, st, B1(l));
+      check_launch();
     } else {
       if (vb.nb > 1) fail(RKL_EINVAL, "batched solves need the one-workgroup coarse tail");
       coarse_solve<T>(P, H, l, o, stop, st);

@@ -7,8 +7,8 @@
 // arrays in LDS:
 //   b of the top tail level (as restricted, its mean removed when periodic,
 //   Sec. 2.3) -> N_pre RKL tau-steps from zero -> residual + 8-point
-//   restriction -> ... -> accelerated RKL coarsest solve (App. A.4, on one
-//   wavefront) -> prolongation + correction -> N_post tau-steps -> ... ->
+//   restriction -> ... -> coarsest solve (direct, or accelerated RKL, App. A.4,
+//   on one wavefront) -> prolongation + correction -> N_post tau-steps -> ... ->
 //   the top level's correction u, written back to HBM.
 // The arithmetic is that of the per-level kernels (stage recurrence of App. A
 // eq. RKL_intermediate_source; ghosts of Sec. 2.3 for the error equation:
@@ -18,7 +18,7 @@
 // neighbour, i.e. the (9, 3, 3, 1)/16 weights of eq. prolongation_example_2D.
 #include <cstring>
 
-#include "kernels.h"
+#include "direct.h"
 
 namespace rkl {
 
@@ -35,6 +35,8 @@ struct TailArgs {
   int nlev, s, n_pre, n_post, periodic, cmax;
   int gs;               // smoother: 0 RKL tau-step, 1 red-black Gauss-Seidel pass
   int flat;             // 1: two-dimensional levels
+  const double* dtab;   // direct coarsest solve: its tables, or nullptr
+  int doff;             // element offset of its two float64 work arrays in the pool (in doubles)
   double ctol;
   CoarseSchedule cs;
   TailLevel<T> lv[TAIL_MAX_LEVELS];
@@ -194,6 +196,64 @@ __device__ void coarse_regs(const TailLevel<T>& V, const int* ssched, const int*
   if (has) U[q] = u;
 }
 
+// Direct solve of the coarsest level (direct.h) by the whole workgroup:
+// B -> U, with D0 and D1 float64 work arrays of n cells and `bad` a flag in LDS
+// that is 0 on entry.  The six matrix applications are separated by barriers,
+// or, when each is a single tile (levels of at most 16 lines and 16 cells along
+// every axis, such as 4^3), run in one wavefront whose LDS operations complete
+// in issue order.  tab: the axis matrices and eigenvalues (LDS or device
+// memory).  A right-hand side whose square overflows or is NaN gives u = 0, as
+// the iteration's stop test does.  Bound by latency: the 35 accelerated
+// tau-steps it stands in for on a 4^3 level took 23 us of the 56 us tail
+// (32^3 Dirichlet solve 1.10 -> 0.92 ms, 256^3 periodic 6.00 -> 5.77 ms), and
+// 487 us on a 10 x 6 x 14 level (160 x 96 x 224 V-cycle 823 -> 268 us).
+template <typename T>
+__device__ void coarse_direct(int nx, int ny, int nz, const double* tab, const T* B, T* U, double* D0, double* D1,
+                              int* bad) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int n = nx * ny * nz, nxy = nx * ny;
+  const double* qx = tab;
+  const double* qy = qx + nx * nx;
+  const double* qz = qy + ny * ny;
+  const double* lx = qz + nz * nz;
+  const double* ly = lx + nx;
+  const double* lz = ly + ny;
+  const bool one = nx <= 16 && ny <= 16 && nz <= 16 && ny * nz <= 16 && nx * nz <= 16 && nxy <= 16;
+  const int nw = one ? 1 : TNT / WAVE;
+  for (int q = tid; q < n; q += TNT) {
+    const double v = (double)B[q];
+    D0[q] = v;
+    if (!(v * v <= 1.7976931348623157e308)) *bad = 1;
+  }
+  __syncthreads();
+  auto keep = [](int, int, double v) { return v; };
+  auto div = [&](int k, int q, double v) {
+    const double lam = lx[q % nx] + ly[q / nx] + lz[k];
+    return lam != 0.0 ? v / lam : 0.0;
+  };
+  auto sync = [&]() {
+    if (one) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    else __syncthreads();
+  };
+  if (!one || w == 0) {
+    axis_apply<false>(D0, D1, qx, nx, 1, ny * nz, w, nw, lane, keep);
+    sync();
+    axis_apply<false>(D1, D0, qy, ny, nx, nx * nz, w, nw, lane, keep);
+    sync();
+    axis_apply<false>(D0, D1, qz, nz, nxy, nxy, w, nw, lane, div);
+    sync();
+    axis_apply<true>(D1, D0, qz, nz, nxy, nxy, w, nw, lane, keep);
+    sync();
+    axis_apply<true>(D0, D1, qy, ny, nx, nx * nz, w, nw, lane, keep);
+    sync();
+    axis_apply<true>(D1, D0, qx, nx, 1, ny * nz, w, nw, lane, keep);
+  }
+  __syncthreads();
+  const bool zero = *bad != 0;
+  for (int q = tid; q < n; q += TNT) U[q] = zero ? (T)0 : (T)D0[q];
+  __syncthreads();
+}
+
 template <typename T>
 __global__ __launch_bounds__(TNT) void k_tail(TailArgs<T> A, const T* __restrict__ b_top, T* __restrict__ u_top,
                                               Batch bt, const int* __restrict__ stop) {
@@ -208,11 +268,16 @@ __global__ __launch_bounds__(TNT) void k_tail(TailArgs<T> A, const T* __restrict
   __shared__ double bc;
   __shared__ int ssched[COARSE_MAX_SCHED];
   __shared__ int scoff[COARSE_MAX_SCHED];
-  __shared__ double scoef[3 * COARSE_MAX_COEF];
+  __shared__ double scoef[3 * COARSE_MAX_COEF];  // stage rows, or the direct solve's tables
+  __shared__ int dbad;
   {
     int cells = 0;  // the pool holds three arrays per level
     for (int l = 0; l < A.nlev; ++l) cells += 3 * A.lv[l].nx * A.lv[l].ny * A.lv[l].nz;
     lds_poison(reinterpret_cast<T*>(pool_raw), cells);
+    if (A.dtab != nullptr) {
+      const TailLevel<T>& C = A.lv[A.nlev - 1];
+      lds_poison(reinterpret_cast<double*>(pool_raw) + A.doff, 2 * C.nx * C.ny * C.nz);
+    }
     lds_poison(red, TNT / WAVE);
     lds_poison(scoef, 3 * COARSE_MAX_COEF);
     lds_poison_sync();
@@ -224,13 +289,24 @@ __global__ __launch_bounds__(TNT) void k_tail(TailArgs<T> A, const T* __restrict
   const int nl = A.nlev;
   // which of a level's two iterate arrays is current: bit l set -> the second
   unsigned swapped = 0u;
-  const int nsched = min(A.cs.nsched, COARSE_MAX_SCHED);
+  const bool direct = A.dtab != nullptr;
+  const int nsched = direct ? 0 : min(A.cs.nsched, COARSE_MAX_SCHED);
   for (int q = tid; q < nsched; q += TNT) {
     ssched[q] = A.cs.sched[q];
     scoff[q] = A.cs.coff[q];
   }
   const int ncoef = nsched > 0 ? min(A.cs.coff[nsched - 1] + A.cs.sched[nsched - 1], COARSE_MAX_COEF) : 0;
   for (int q = tid; q < 3 * ncoef; q += TNT) scoef[q] = A.cs.coef[q];
+  const double* dtab = A.dtab;
+  if (direct) {
+    const TailLevel<T>& C = A.lv[nl - 1];
+    const int nt = C.nx * (C.nx + 1) + C.ny * (C.ny + 1) + C.nz * (C.nz + 1);
+    if (nt <= 3 * COARSE_MAX_COEF) {  // long axes keep their tables in device memory
+      for (int q = tid; q < nt; q += TNT) scoef[q] = A.dtab[q];
+      dtab = scoef;
+    }
+    if (tid == 0) dbad = 0;
+  }
 
   auto nof = [&](int l) { return A.lv[l].nx * A.lv[l].ny * A.lv[l].nz; };
   auto bptr = [&](int l) { return pool + A.lv[l].off + 2 * nof(l); };
@@ -401,7 +477,11 @@ __global__ __launch_bounds__(TNT) void k_tail(TailArgs<T> A, const T* __restrict
   // this wavefront touches the level's arrays, and the LDS operations of one
   // wavefront complete in issue order, so wavefront-scope fences (compiler
   // ordering) separate the stages.
-  if (nof(nl - 1) <= WAVE) {
+  if (direct) {
+    const TailLevel<T>& C = A.lv[nl - 1];
+    double* D = reinterpret_cast<double*>(pool_raw) + A.doff;
+    coarse_direct<T>(C.nx, C.ny, C.nz, dtab, bptr(nl - 1), curp(nl - 1), D, D + nof(nl - 1), &dbad);
+  } else if (nof(nl - 1) <= WAVE) {
     if (tid < WAVE)
       coarse_regs<T>(A.lv[nl - 1], ssched, scoff, scoef, nsched, per, A.ctol, A.cmax, bptr(nl - 1), curp(nl - 1));
     __syncthreads();
@@ -628,20 +708,29 @@ __global__ __launch_bounds__(TNT) void k_tail(TailArgs<T> A, const T* __restrict
   }
 }
 
+// bytes of the levels' arrays, rounded up so that the direct solve's float64
+// work arrays may follow
 template <typename T>
-size_t tail_lds_bytes(const TailShape& ts) {
+size_t tail_pool_bytes(const TailShape& ts) {
   size_t cells = 0;
   for (int l = 0; l < ts.nlev; ++l) cells += 3 * (size_t)ts.nx[l] * ts.ny[l] * ts.nz[l];
-  return cells * sizeof(T);
+  return (cells * sizeof(T) + 15) / 16 * 16;
+}
+size_t tail_bottom(const TailShape& ts) {
+  const int l = ts.nlev - 1;
+  return (size_t)ts.nx[l] * ts.ny[l] * ts.nz[l];
+}
+template <typename T>
+size_t tail_lds_bytes(const TailShape& ts, bool direct) {
+  return tail_pool_bytes<T>(ts) + (direct ? 2 * tail_bottom(ts) * sizeof(double) : 0);
 }
 
 template <typename T>
-bool tail_fits(const TailShape& ts, int s) {
-  if (ts.nlev < 2 || ts.nlev > TAIL_MAX_LEVELS || s > TAIL_MAX_S) return false;
+bool tail_fits(const TailShape& ts, int s, bool direct) {
+  if (ts.nlev < (direct ? 1 : 2) || ts.nlev > TAIL_MAX_LEVELS || s > TAIL_MAX_S) return false;
   const size_t top = (size_t)ts.nx[0] * ts.ny[0] * ts.nz[0];
-  const size_t bottom = (size_t)ts.nx[ts.nlev - 1] * ts.ny[ts.nlev - 1] * ts.nz[ts.nlev - 1];
-  if (top > (size_t)TAIL_MAX_CELLS || bottom > (size_t)(4 * WAVE)) return false;
-  return tail_lds_bytes<T>(ts) <= TAIL_MAX_LDS;
+  if (top > (size_t)TAIL_MAX_CELLS || tail_bottom(ts) > (size_t)(direct ? DIRECT_LDS_CELLS : 4 * WAVE)) return false;
+  return tail_lds_bytes<T>(ts, direct) <= TAIL_MAX_LDS;
 }
 
 // Raise the dynamic LDS limit of both tail kernels (once per process; a
@@ -659,7 +748,7 @@ void tail_prepare() {
 template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
-                 hipStream_t st, const Batch& bt, int gs) {
+                 hipStream_t st, const Batch& bt, int gs, const DirectTables* dir) {
   TailArgs<T> A;
   std::memset(&A, 0, sizeof(A));
   A.gs = gs;
@@ -690,16 +779,22 @@ void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int
       V.c[j] = (T)smooth[l][j].c;
     }
   }
-  const size_t shm = tail_lds_bytes<T>(ts);
+  if (dir != nullptr) {
+    A.dtab = dir->tab;
+    A.doff = (int)(tail_pool_bytes<T>(ts) / sizeof(double));
+  }
+  const size_t shm = tail_lds_bytes<T>(ts, dir != nullptr);
   tail_prepare();
   hipLaunchKernelGGL(k_tail<T>, dim3(bt.nb), dim3(TNT), shm, st, A, b_top, u_top, bt, stop);
 }
 
-template bool tail_fits<double>(const TailShape&, int);
-template bool tail_fits<float>(const TailShape&, int);
+template bool tail_fits<double>(const TailShape&, int, bool);
+template bool tail_fits<float>(const TailShape&, int, bool);
 template void launch_tail<double>(const TailShape&, const StageCoef* const*, int, int, int, int, CoarseSchedule,
-                                  double, int, const double*, double*, const int*, hipStream_t, const Batch&, int);
+                                  double, int, const double*, double*, const int*, hipStream_t, const Batch&, int,
+                                  const DirectTables*);
 template void launch_tail<float>(const TailShape&, const StageCoef* const*, int, int, int, int, CoarseSchedule,
-                                 double, int, const float*, float*, const int*, hipStream_t, const Batch&, int);
+                                 double, int, const float*, float*, const int*, hipStream_t, const Batch&, int,
+                                 const DirectTables*);
 
 }  // namespace rkl
