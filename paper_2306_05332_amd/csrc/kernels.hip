@@ -129,49 +129,147 @@ __global__ __launch_bounds__(NT) void k_fold_faces(int nx, int ny, int nz, doubl
 // layers: periodic wrap, or odd reflection about the Dirichlet face value g
 // (phi_{-m} = 2 g - phi_{m-1}, m = 1, 2; g = 0 without face data).  ihz = 0
 // (hz = inf, a two-dimensional grid) gives g_z = 0 without z reads.
-__global__ __launch_bounds__(NT) void k_gradient(int nx, int ny, int nz, double ihx, double ihy, double ihz,
-                                                 int periodic, const double* __restrict__ faces,
-                                                 const double* __restrict__ phi, double* __restrict__ gx,
-                                                 double* __restrict__ gy, double* __restrict__ gz, int kz) {
-  const int i = blockIdx.x * TX + threadIdx.x;
-  const int j = blockIdx.y * TY + threadIdx.y;
-  const int k0 = blockIdx.z * kz;
-  if (i >= nx || j >= ny) return;
+//
+// A wavefront holds 64 columns of GR rows and marches up a few planes with the
+// five z values of every column in registers; the rows serve each other as y
+// neighbours.  The neighbours' offsets, wrapped or mirrored, are set once; a
+// Dirichlet ghost is turned around after its load under branches that only the
+// wavefronts at a face take.  8 bytes are read and 24 written per cell: bound
+// by HBM (a kernel that only streams these words takes 91-100 us at 256^3).
+// Chunks are short and workgroups ordered plane by plane, so that the three
+// output streams advance as compact fronts: 119 us at 256^3 on inputs that
+// come from HBM, against 164 us in chunks of 32 planes and 180 us with one row
+// a lane; within a chunk neighbouring rows stay on one XCD.  The outputs take
+// non-temporal stores (3-10 % faster from 64^3 to 384^3).  Whole call at 256^3
+// with face data: 384 -> 148 us from one cell a lane with every neighbour
+// branched on.
+constexpr int GR = 4, GW = 4;  // rows per wavefront, wavefronts per workgroup
+__global__ __launch_bounds__(WAVE * GW) void k_gradient(int nx, int ny, int nz, double ihx, double ihy, double ihz,
+                                                   int periodic, const double* __restrict__ faces,
+                                                   const double* __restrict__ phi, double* __restrict__ gx,
+                                                   double* __restrict__ gy, double* __restrict__ gz, int kz,
+                                                   unsigned gx_tiles, unsigned per) {
+  const unsigned chunk = blockIdx.x / per;
+  unsigned tile = blockIdx.x - chunk * per;
+  if ((per & 7) == 0) tile = (tile & 7) * (per >> 3) + (tile >> 3);
+  const int i = (int)(tile % gx_tiles) * WAVE + (threadIdx.x & (WAVE - 1));
+  const int j0 = ((int)(tile / gx_tiles) * GW + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE)) * GR;
+  const int k0 = (int)chunk * kz;
+  if (i >= nx || j0 >= ny) return;
   const int k1 = min(k0 + kz, nz);
-  const size_t sy = (size_t)nx, sz = (size_t)nx * ny;
+  const size_t sz = (size_t)nx * ny;
+  // cell that stands for position q of an axis of n cells: wrapped (also on
+  // axes shorter than the stencil) or, beyond a Dirichlet face, the mirror cell
+  auto cell = [&](int q, int n) -> int {
+    if (q >= 0 && q < n) return q;
+    if (periodic) return ((q % n) + n) % n;
+    return q < 0 ? -q - 1 : 2 * n - 1 - q;
+  };
   auto fv = [&](int face, size_t idx) -> double {
     return faces != nullptr ? faces[face_off(face, nx, ny, nz) + idx] : 0.0;
   };
+  auto deriv = [&](double m2, double m1, double p1, double p2, double ih) {
+    return -(4.0 / 3.0) * (p1 - m1) * (0.5 * ih) + (1.0 / 3.0) * (p2 - m2) * (0.25 * ih);
+  };
+  constexpr int D[4] = {-2, -1, 1, 2};
+  unsigned ox[4];     // byte offsets of the x neighbours' columns
+  size_t oy[GR + 4];  // rows j0 - 2 .. j0 + GR + 1 (those past the last ghost row repeat it)
+  const unsigned oi = (unsigned)i * 8u;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) ox[d] = (unsigned)cell(i + D[d], nx) * 8u;
+#pragma unroll
+  for (int r = 0; r < GR + 4; ++r) oy[r] = (size_t)cell(min(j0 + r - 2, ny + 1), ny) * nx;
+  const bool xface = !periodic && (i < 2 || i >= nx - 2);
+  const bool yface = !periodic && (j0 < 2 || j0 + GR + 2 > ny);
+  const bool flat = ihz == 0.0;
+  // value at byte offset o of a row (a wave-uniform address and a lane's offset)
+  auto ld = [](const double* row, unsigned o) -> double { return *(const double*)((const char*)row + o); };
+  double z[GR][5];  // planes k - 2 .. k + 2 of the lane's columns
+  double zn[GR];    // plane k + 3, loaded an iteration ahead
+  auto zload = [&](int q) {  // plane q (its mirror beyond a face) into zn
+    const double* P = phi + (size_t)cell(q, nz) * sz;
+#pragma unroll
+    for (int r = 0; r < GR; ++r) zn[r] = ld(P + oy[r + 2], oi);
+  };
+  auto zpush = [&](int q) {  // zn, plane q, into the queue with its ghosts
+#pragma unroll
+    for (int r = 0; r < GR; ++r) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) z[r][d] = z[r][d + 1];
+      z[r][4] = zn[r];
+    }
+    if (!periodic && (q < 0 || q >= nz)) {
+#pragma unroll
+      for (int r = 0; r < GR; ++r) z[r][4] = 2.0 * fv(q < 0 ? 4 : 5, oy[r + 2] + i) - z[r][4];
+    }
+  };
+  if (flat) {
+    zload(k0);
+#pragma unroll
+    for (int r = 0; r < GR; ++r) z[r][0] = z[r][1] = z[r][2] = z[r][3] = z[r][4] = zn[r];
+  } else {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      zload(k0 - 2 + d);
+      zpush(k0 - 2 + d);
+    }
+    zload(k0 + 2);
+  }
   for (int k = k0; k < k1; ++k) {
-    const size_t c = (size_t)k * sz + (size_t)j * sy + i;
-    // value at offset d in {-2,-1,1,2} along an axis of length n at position p
-    auto along = [&](int p, int n, int d, size_t stride, int flo, int fhi, size_t fidx) -> double {
-      const int q = p + d;
-      if (q >= 0 && q < n) return phi[c + (ptrdiff_t)d * (ptrdiff_t)stride];
-      if (periodic) {
-        const int w = ((q % n) + n) % n;  // also for axes shorter than the stencil
-        return phi[c + (ptrdiff_t)(w - p) * (ptrdiff_t)stride];
+    const double* P = phi + (size_t)k * sz;
+    if (!flat) zpush(k + 2);
+    double x[GR][4], y[GR + 4];
+#pragma unroll
+    for (int r = 0; r < GR; ++r) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) x[r][d] = ld(P + oy[r + 2], ox[d]);
+    }
+#pragma unroll
+    for (int r = 0; r < GR + 4; ++r)
+      y[r] = (r < 2 || r >= GR + 2) ? ld(P + oy[r], oi) : z[r >= 2 && r < GR + 2 ? r - 2 : 0][2];
+    double glo[GR], ghi[GR];  // face values beside the lane's rows
+#pragma unroll
+    for (int r = 0; r < GR; ++r) glo[r] = ghi[r] = 0.0;
+    if (xface && faces != nullptr) {
+#pragma unroll
+      for (int r = 0; r < GR; ++r) {
+        const size_t fx = (size_t)k * ny + min(j0 + r, ny - 1);
+        if (i < 2) glo[r] = fv(0, fx);
+        if (i >= nx - 2) ghi[r] = fv(1, fx);
       }
-      if (q < 0) {
-        const int m = -q;  // ghost layer m: mirror cell m - 1
-        return 2.0 * fv(flo, fidx) - phi[c + (ptrdiff_t)(m - 1 - p) * (ptrdiff_t)stride];
+    }
+    // the plane from HBM is issued last: loads complete in issue order, so the
+    // cached ones above are not waited for through it
+    __builtin_amdgcn_sched_barrier(0);
+    if (!flat && k + 1 < k1) zload(k + 3);
+    __builtin_amdgcn_sched_barrier(0);
+    if (xface) {
+#pragma unroll
+      for (int r = 0; r < GR; ++r) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          if (i + D[d] < 0) x[r][d] = 2.0 * glo[r] - x[r][d];
+          if (i + D[d] >= nx) x[r][d] = 2.0 * ghi[r] - x[r][d];
+        }
       }
-      const int m = q - (n - 1);  // mirror cell n - m
-      return 2.0 * fv(fhi, fidx) - phi[c + (ptrdiff_t)(n - m - p) * (ptrdiff_t)stride];
-    };
-    auto deriv = [&](double m2, double m1, double p1, double p2, double ih) {
-      return -(4.0 / 3.0) * (p1 - m1) * (0.5 * ih) + (1.0 / 3.0) * (p2 - m2) * (0.25 * ih);
-    };
-    const size_t fx = (size_t)k * ny + j, fy = (size_t)k * nx + i, fz = (size_t)j * nx + i;
-    gx[c] = deriv(along(i, nx, -2, 1, 0, 1, fx), along(i, nx, -1, 1, 0, 1, fx), along(i, nx, 1, 1, 0, 1, fx),
-                  along(i, nx, 2, 1, 0, 1, fx), ihx);
-    gy[c] = deriv(along(j, ny, -2, sy, 2, 3, fy), along(j, ny, -1, sy, 2, 3, fy), along(j, ny, 1, sy, 2, 3, fy),
-                  along(j, ny, 2, sy, 2, 3, fy), ihy);
-    if (ihz == 0.0)
-      gz[c] = 0.0;
-    else
-      gz[c] = deriv(along(k, nz, -2, sz, 4, 5, fz), along(k, nz, -1, sz, 4, 5, fz), along(k, nz, 1, sz, 4, 5, fz),
-                    along(k, nz, 2, sz, 4, 5, fz), ihz);
+    }
+    if (yface) {
+      const size_t fy = (size_t)k * nx + i;
+#pragma unroll
+      for (int r = 0; r < GR + 4; ++r) {
+        if (j0 + r - 2 < 0) y[r] = 2.0 * fv(2, fy) - y[r];
+        if (j0 + r - 2 >= ny) y[r] = 2.0 * fv(3, fy) - y[r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < GR; ++r) {
+      if (j0 + r >= ny) break;
+      const size_t c = (size_t)k * sz + oy[r + 2];
+      auto put = [&](double* row, double v) { __builtin_nontemporal_store(v, (double*)((char*)row + oi)); };
+      put(gx + c, deriv(x[r][0], x[r][1], x[r][2], x[r][3], ihx));
+      put(gy + c, deriv(y[r], y[r + 1], y[r + 3], y[r + 4], ihy));
+      put(gz + c, flat ? 0.0 : deriv(z[r][0], z[r][1], z[r][3], z[r][4], ihz));
+    }
   }
 }
 
@@ -521,9 +619,13 @@ void launch_fold_faces(int nx, int ny, int nz, double hx, double hy, double hz, 
 
 void launch_gradient(int nx, int ny, int nz, double hx, double hy, double hz, int periodic, const double* faces,
                      const double* phi, double* gx, double* gy, double* gz, hipStream_t st) {
-  const int kz = ((size_t)nx * ny * nz < ((size_t)1 << 21)) ? 1 : KZ;
-  hipLaunchKernelGGL(k_gradient, grid3(nx, ny, nz, kz), dim3(TX, TY), 0, st, nx, ny, nz, 1.0 / hx, 1.0 / hy,
-                     1.0 / hz, periodic, faces, phi, gx, gy, gz, kz);
+  // chunks of four planes (measured: 2, 3, 5 and 8 planes are 4-18 % slower at
+  // 256^3), shorter where that leaves fewer than 2048 wavefronts, two per SIMD
+  const unsigned gxt = (nx + WAVE - 1) / WAVE, per = gxt * ((ny + GW * GR - 1) / (GW * GR));
+  const size_t waves = (size_t)per * GW * nz;
+  const int kz = (int)std::max<size_t>(1, std::min<size_t>(4, waves / 2048));
+  hipLaunchKernelGGL(k_gradient, dim3(per * (unsigned)((nz + kz - 1) / kz)), dim3(WAVE * GW), 0, st, nx, ny, nz,
+                     1.0 / hx, 1.0 / hy, 1.0 / hz, periodic, faces, phi, gx, gy, gz, kz, gxt, per);
 }
 
 template <typename T>
