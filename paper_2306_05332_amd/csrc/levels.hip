@@ -48,7 +48,7 @@ void vcycle_impl(Plan& P, const rkl_opts& o, const T* b, T* phi, double* rel_out
   }();
   T* cur = phi;
   T* alt = level0_alt<T>(P);
-  vcycle_from<T>(P, H, cur, alt, b, nullptr, 0, o, nullptr, st, VBatch{1, 0, 0, P.dscal});
+  vcycle_from<T>(P, H, cur, alt, b, nullptr, 0, o, nullptr, st, VBatch{1, 0, 0, P.dscal}, false);
   copy_back<T>(phi, cur, P.lv[0].n, st);
   if (rel_out) {
     const LevelView<T> V0 = view<T>(P.lv[0], P.periodic, nullptr);

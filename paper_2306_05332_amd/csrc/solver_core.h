@@ -485,9 +485,21 @@ struct VBatch {
   double* dirw = nullptr;  // direct coarsest solve's scratch (nullptr: the plan's own)
 };
 
+//
+// Periodic compatibility (Sec. 2.3): the restricted residual of a mean-free
+// right-hand side is mean-free up to rounding, since the periodic M sums to
+// zero and the restriction keeps the mean.  So one removal per cycle serves
+// every level below it: the solves, whose f is made mean-free, leave it to the
+// tail (in LDS) or to the direct coarsest solve (which drops the constant
+// mode), and a right-hand side used as given (mean_free = false) has it on
+// level 1.  What rounding leaves shifts a level's iterate by a constant of
+// rounding size, which M annihilates and the solves' final mean removal
+// drops.  The iteration on a coarsest level outside the tail, whose stop test
+// sees the mean, removes it there.  (A removal on every level took 19 us of
+// the 470 us cycle at 256^3 float64.)
 template <typename T>
 void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const double* faces0, int pre_done,
-                 const rkl_opts& o, const int* stop, hipStream_t st, const VBatch& vb) {
+                 const rkl_opts& o, const int* stop, hipStream_t st, const VBatch& vb, bool mean_free = true) {
   const int L = P.L();
   double* part = vb.part ? vb.part : P.part;
   auto V = [&](int l) { return view<T>(P.lv[l], P.periodic, l == 0 ? faces0 : nullptr); };
@@ -534,7 +546,8 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
       check_launch();
       break;
     }
-    if (P.periodic) {  // coarse right-hand side made mean-free (its sum: the restriction's partials)
+    // coarse right-hand side made mean-free (its sum: the restriction's partials)
+    if (P.periodic && ((l == 1 && !mean_free) || (l == L - 1 && !direct))) {
       Batch bs{vb.nb, (long long)C.n, 0, vb.stop_stride, vb.part_stride};
       launch_sub_mean_part<T>(H.b[l], C.n, part, pairs, 2, 1, (double)C.n, stop, st, bs);
       check_launch();
