@@ -160,7 +160,7 @@ void class_iteration_direct(ClassPlan& C, const rkl_opts& o, hipStream_t st, int
   double *cur = nullptr, *alt = nullptr;
   tau_keep<double>(P, V0, bufs[ia], bufs[(ia + 1) % 3], bufs[(ia + 2) % 3], cur, alt, C.f0,
                    pair0 ? F.smooth2 : F.smooth, C.part, stop, st, gs, b0);
-  const int nblk = (int)(gs ? gsrb_blocks<double>(V0) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s));
+  const int nblk = (int)(gs ? gsrb_blocks<double>(V0, nb) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s, nb));
   launch_check(C.part, nblk, 1, C.res0sq, o.tol, o.max_cycles, 1.0, C.conv, st, Batch{nb, 0, 0, 0, ps});
   check_launch();
   vcycle_from<double>(P, H, cur, alt, C.f0, nullptr, pair0 ? 2 : 1, o, stop, st,

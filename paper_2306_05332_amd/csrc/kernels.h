@@ -105,7 +105,8 @@ constexpr int FUSED_MAX_S = 4;
 template <typename T>
 bool fused_tau_supported(const LevelView<T>& L, int s);
 template <typename T>
-size_t fused_tau_blocks(const LevelView<T>& L, int s);  // partial sums written when part != nullptr
+// partial sums (per member of a batch of nb) written when part != nullptr
+size_t fused_tau_blocks(const LevelView<T>& L, int s, int nb = 1);
 // u == nullptr: the input iterate is zero
 template <typename T>
 bool launch_fused_tau(const LevelView<T>& L, const T* u, const T* b, T* out, int s,
@@ -173,7 +174,7 @@ struct FusedChoice {
 template <typename T>
 bool fused_variant_ok(int variant, int s);
 template <typename T>
-FusedChoice fused_choice(const LevelView<T>& L, int s);
+FusedChoice fused_choice(const LevelView<T>& L, int s, int nb = 1);  // nb: members of the batch
 template <typename T>
 size_t fused_tau_blocks_as(const LevelView<T>& L, FusedChoice c, int s);
 // workgroups per z chunk of a strip variant on this level (0: not a strip
@@ -250,7 +251,7 @@ template <typename T>
 bool launch_gsrb_fused(const LevelView<T>& L, const T* u, const T* b, T* out, double omega, double* part,
                        const int* stop, hipStream_t st, const Batch& bt = single_batch());
 template <typename T>
-size_t gsrb_blocks(const LevelView<T>& L);  // partial sums written by launch_gsrb_fused
+size_t gsrb_blocks(const LevelView<T>& L, int nb = 1);  // partial sums written by launch_gsrb_fused
 // One colour per launch, any level size: uout = uin with the cells of
 // `colour` updated from uin (two launches make one iteration).
 template <typename T>

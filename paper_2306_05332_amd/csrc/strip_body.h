@@ -397,6 +397,13 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
     }
     return sz;
   };
+  // 3 a + b, rounded once: explicit, so that a chunk's first planes and its
+  // march, compiled apart, give the same bits wherever the chunks are cut
+  // (a batch member's answer is the single solve's)
+  auto fma3 = [](T a, T b) -> T {
+    if constexpr (sizeof(T) == 8) return __builtin_fma(3.0, a, b);
+    else return __builtin_fmaf(3.0f, a, b);
+  };
   // PRO: E[i] = 64 x (coarse plane C interpolated in x and y onto held row i),
   // ghost signs included (x, then y, as eq. prolongation_example_3D weighs)
   auto cfin = [&](const T(&C)[PRO && !PDMA ? NC : 1][2], T sz, T(&E)[PRO ? NU : 1]) {
@@ -410,15 +417,15 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           X[c] = (T)0;
-          if (cneed(c)) X[c] = (sz * csg[c]) * ((T)3 * (T)cdma[w][c][cofp] + sxn * (T)cdma[w][c][cofn]);
+          if (cneed(c)) X[c] = (sz * csg[c]) * fma3((T)cdma[w][c][cofp], sxn * (T)cdma[w][c][cofn]);
         }
       } else {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) X[c] = (sz * csg[c]) * ((T)3 * C[c][0] + sxn * C[c][1]);
+        for (int c = 0; c < NC; ++c) X[c] = (sz * csg[c]) * fma3(C[c][0], sxn * C[c][1]);
       }
 #pragma unroll
       for (int i = 0; i < NU; ++i)
-        if (gl(i)) E[i] = (T)3 * X[cpar(i)] + X[cnb(i)];
+        if (gl(i)) E[i] = fma3(X[cpar(i)], X[cnb(i)]);
     }
   };
   // PRO: EA / EB hold the interpolants of coarse planes Kl(p) = fdiv2(p - 1)
@@ -429,8 +436,13 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
 #pragma unroll
   for (int i = 0; i < (PRO ? NU : 1); ++i) EA[i] = EB[i] = (T)0;
   auto corr = [&](T v, int p, int i) -> T {  // v + (P e) at plane p, held row i
-    if constexpr (PRO) return v + ((p & 1) ? ((T)3 * EA[i] + EB[i]) : (EA[i] + (T)3 * EB[i])) * (T)(1.0 / 64.0);
-    else return v;
+    if constexpr (PRO) {
+      const T ea = EA[i], eb = EB[i];
+      const T odd = fma3(ea, eb), even = fma3(eb, ea);
+      return v + ((p & 1) ? odd : even) * (T)(1.0 / 64.0);
+    } else {
+      return v;
+    }
   };
   // PRO: make EA / EB current for fine plane p, given that they were for p - 1
   auto pro_step = [&](int p) {

@@ -40,7 +40,7 @@ static void launch_strip_pro_k(const LevelView<T>& L, int target, const T* u, co
   if (target <= 0) {
     static std::atomic<int> slots[64];
     const int per = strip_grid(S, R, WY, L.nx, L.ny, L.nz, 1, false, false).per;
-    target = std::max(1, resident_wgs(kern, 64 * WY, slots) / per) * per;
+    target = std::max(1, resident_wgs(kern, 64 * WY, slots) / (per * bt.nb)) * per;
   }
   const StripGrid g = strip_grid(S, R, WY, L.nx, L.ny, L.nz, target, false, false);
   hipLaunchKernelGGL(kern, dim3(g.nblk, bt.nb), dim3(64 * WY), 0, st, L, u, e, b, out, fc, g.zc, g.gx, g.gy, g.nblk,

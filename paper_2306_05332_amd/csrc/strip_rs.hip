@@ -30,7 +30,8 @@ __global__ __launch_bounds__(64 * WY, (strip_min_waves<T, R, WY>())) void k_tau_
       nullptr, bc);
 }
 
-// target: workgroups the device holds at once; the z chunks are as many as
+// target: workgroups the device holds at once (a batch's members share
+// them); the z chunks are as many as
 // fit in one such wave of workgroups, since a partial second wave would cost
 // nearly a whole pass
 StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target) {
@@ -59,9 +60,8 @@ static int launch_rs_k(const LevelView<T>& L, const T* u, const T* b, T* out, T*
                        double* part, const int* stop, const Batch& bt, hipStream_t st) {
   static std::atomic<int> slots[64];
   auto kern = k_tau_strip_rs<T, S, R, WY, PER, SHY, NT>;
-  // the grid depends on the level only, not on the batch size, so that a
-  // batch member's partial sums (and its answer) are the single solve's
-  const StripGrid g = strip_grid_rs(S, R, WY, L.nx, L.ny, L.nz, resident_wgs(kern, 64 * WY, slots));
+  const StripGrid g = strip_grid_rs(S, R, WY, L.nx, L.ny, L.nz,
+                                    std::max(1, resident_wgs(kern, 64 * WY, slots) / bt.nb));
   hipLaunchKernelGGL(kern, dim3(g.nblk, bt.nb), dim3(64 * WY), 0, st, L, u, b, out, bc, fc, g.zc, g.gx, g.gy, g.nblk,
                      part, bt, stop);
   return g.nblk;
