@@ -641,17 +641,49 @@ int tune_generation() {
   return g_tune_gen;
 }
 
-// Built-in choice (what the tuner picked on gfx950 for most shapes): the
-// strip kernel, 8-row strips for large float64 levels and 4-row strips
-// otherwise; stage counts the strip kernel is not built for take the
-// z-queue kernel on large levels and the LDS-ring kernel on small ones.
+// z chunks of a strip shape such that its workgroups fill the device's slots
+// once, or the fewest whole times that keep chunks within 64 planes: a
+// workgroup more than a whole filling costs nearly another march of the level.
+static FusedChoice strip_filling(int variant, int s, int nx, int ny, int nz, int slots) {
+  int R, WY;
+  strip_shape(variant, R, WY);
+  const int per = strip_grid(s, R, WY, nx, ny, nz, 1).per;
+  const int need = (nz + 63) / 64;
+  int chunks = 0;
+  for (int k = 1; chunks < need; ++k) chunks = (int)((long long)k * slots / per);
+  return FusedChoice{variant, chunks * per};
+}
+
+// Built-in choice for levels without a timed entry.  Lines drawn from timing
+// every strip shape and chunk length on 25 shapes from 20 x 24 x 28 to 320 x
+// 384 x 384 (s = 2); means of the gain over four-row strips at 1024 workgroups
+// (large periodic float64 levels: eight-row ones), which stood here before:
+//  * float64, periodic: stacked two-row strips, two workgroups per CU, from
+//    1.25 million cells (256^3 101 -> 82 us, 190 x 256 x 384 117 -> 96,
+//    160^3 25 -> 23), five-row one-wavefront strips, one per SIMD, below (100^3
+//    16.4 -> 11.1, 64^3 8.9 -> 7.4); 1.19 x, within 3.5 % of the best shape;
+//  * float64, Dirichlet: the stacked strips where the sweep's arrays overflow
+//    the last-level cache (256^3 109 -> 92), four-row strips at two workgroups
+//    per CU below (192^3 45 -> 38); 1.08 x;
+//  * float32: beyond that cache stacked eight-row (periodic, 320 x 384 x 384
+//    164 -> 125) or four-row strips (Dirichlet, 164 -> 152), else four-row strips
+//    at four workgroups per CU, small periodic levels five-row ones; 1.06 x
+//    periodic, 1.01 x Dirichlet.
+// Stage counts the strip kernel is not built for take the z-queue kernel on
+// large levels and the LDS-ring kernel on small ones.
 template <typename T>
 FusedChoice fused_heuristic(const LevelView<T>& L, int s) {
   if (level_is_2d(L)) return FusedChoice{(sizeof(T) == 8 && s <= 2) ? FV_STRIP2D_8 : FV_STRIP2D_4, 2048};
   if (fused_variant_ok<T>(FV_STRIP_4x4, s)) {
-    const bool big = (size_t)L.nx * L.ny * L.nz >= ((size_t)192 * 192 * 192);
-    if (sizeof(T) == 8 && L.periodic && big) return FusedChoice{FV_STRIP_8x4, 1024};
-    return FusedChoice{FV_STRIP_4x4, 1024};
+    const size_t n = (size_t)L.nx * L.ny * L.nz;
+    const bool big = 3 * sizeof(T) * n > ((size_t)256 << 20);
+    auto fill = [&](int variant, int slots) { return strip_filling(variant, s, L.nx, L.ny, L.nz, slots); };
+    if (sizeof(T) == 8) {
+      if (s <= 2 && (big || (L.periodic && n >= 1250000))) return fill(FV_STRIPYX_2x8, 512);
+      return L.periodic ? fill(FV_STRIP_5x1, 1024) : fill(FV_STRIP_4x4, 512);
+    }
+    if (big) return L.periodic ? fill(FV_STRIPYX_8x4, 512) : fill(FV_STRIPYX_4x8, 512);
+    return L.periodic && n < 1250000 ? fill(FV_STRIP_5x1, 1024) : fill(FV_STRIP_4x4, 1024);
   }
   if (fused_variant_ok<T>(FV_ZQ_64x32, s) && L.nx >= 128 && L.ny >= 128 && L.nz >= 64) return FusedChoice{FV_ZQ_64x32, 256};
   return FusedChoice{FV_RING_64x4, 1024};
