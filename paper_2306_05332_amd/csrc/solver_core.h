@@ -497,9 +497,14 @@ struct VBatch {
 // drops.  The iteration on a coarsest level outside the tail, whose stop test
 // sees the mean, removes it there.  (A removal on every level took 19 us of
 // the 470 us cycle at 256^3 float64.)
+//
+// home (optional): the array that the last level-0 relaxation writes, neither
+// cur0 nor read by it; for n_post = 1 and a level whose relaxations are single
+// passes.
 template <typename T>
 void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const double* faces0, int pre_done,
-                 const rkl_opts& o, const int* stop, hipStream_t st, const VBatch& vb, bool mean_free = true) {
+                 const rkl_opts& o, const int* stop, hipStream_t st, const VBatch& vb, bool mean_free = true,
+                 T* home = nullptr) {
   const int L = P.L();
   double* part = vb.part ? vb.part : P.part;
   auto V = [&](int l) { return view<T>(P.lv[l], P.periodic, l == 0 ? faces0 : nullptr); };
@@ -572,6 +577,7 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
     T*& cu = (l == 0) ? cur0 : H.u[l];
     T*& ca = (l == 0) ? alt0 : H.t[l];
     const T* bl = (l == 0) ? b0 : H.b[l];
+    if (l == 0 && home != nullptr) ca = home;
     const Lev& F = P.lv[l];
     // prolongation + correction (Sec. 2.1 steps 4-5) fused into the first
     // post-smoothing tau-step where the level's strip kernel allows it
