@@ -324,6 +324,7 @@ hipGraphExec_t batch_graph(std::vector<ClassPlan*>& cls, const rkl_opts& o, int 
   for (auto* c : cls) sig.cls.push_back({c, iters});
   if (g_graph && g_graph->sig == sig) return g_graph->exec;
   tail_prepare();
+  tail_col_prepare();
   direct_prepare();
   auto G = std::make_unique<GraphCache>();
   G->sig = sig;

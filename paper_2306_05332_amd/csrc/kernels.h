@@ -276,9 +276,13 @@ const char* fused_variant_name(int variant);
 // Direct solve of the coarsest level (direct.h, direct.hip): the axes'
 // orthonormal eigenvectors and eigenvalues, `tab` (device) holding the rows of
 // Qx, Qy and Qz (nx^2 + ny^2 + nz^2 values), then the nx + ny + nz eigenvalues.
+// dense (device): the inverse itself, rows padded to DIRECT_DENSE columns and as
+// many rows, on levels of at most that many cells; else nullptr.
+constexpr int DIRECT_DENSE = 64;
 struct DirectTables {
   int nx, ny, nz;
   const double* tab;
+  const double* dense;
 };
 constexpr int DIRECT_LDS_CELLS = 2048;  // larger levels take the multi-workgroup form
 bool direct_axes_ok(int nx, int ny, int nz);
@@ -312,5 +316,12 @@ template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
                  hipStream_t st, const Batch& bt = single_batch(), int gs = 0, const DirectTables* dir = nullptr);
+// The same tail in column form (tail_col.hip); false when the tail does not
+// have it (the caller takes launch_tail).
+void tail_col_prepare();
+template <typename T>
+bool launch_tail_col(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
+                     const T* b_top, T* u_top, const int* stop, hipStream_t st, const Batch& bt,
+                     const DirectTables& dir);
 
 }  // namespace rkl

@@ -274,6 +274,34 @@ static void axis_modes(int n, double h, bool periodic, double* Q, double* lam) {
   }
 }
 
+// The inverse of a coarsest operator of at most DIRECT_DENSE cells from its
+// axis tables (the layout of DirectTables::tab), constant mode dropped, padded
+// with zeros to DIRECT_DENSE^2.
+static std::vector<double> dense_inverse(const double* tab, int nx, int ny, int nz) {
+  const double* qx = tab;
+  const double* qy = qx + nx * nx;
+  const double* qz = qy + ny * ny;
+  const double* lx = qz + nz * nz;
+  const double* ly = lx + nx;
+  const double* lz = ly + ny;
+  const int n = nx * ny * nz;
+  std::vector<double> g((size_t)DIRECT_DENSE * DIRECT_DENSE, 0.0);
+  auto mode = [&](int a, int b, int c, int q) {
+    return qx[a * nx + q % nx] * qy[b * ny + (q / nx) % ny] * qz[c * nz + q / (nx * ny)];
+  };
+  for (int c = 0; c < nz; ++c)
+    for (int b = 0; b < ny; ++b)
+      for (int a = 0; a < nx; ++a) {
+        const double lam = lx[a] + ly[b] + lz[c];
+        if (lam == 0.0) continue;
+        for (int p = 0; p < n; ++p) {
+          const double v = mode(a, b, c, p) / lam;
+          for (int q = 0; q < n; ++q) g[(size_t)p * DIRECT_DENSE + q] += v * mode(a, b, c, q);
+        }
+      }
+  return g;
+}
+
 Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec) {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
@@ -369,7 +397,13 @@ Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec)
     }
     double* d_tab = P->alloc<double>(tab.size());
     HIPCHK(hipMemcpy(d_tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-    P->direct = DirectTables{C.nx, C.ny, C.nz, d_tab};
+    double* d_dense = nullptr;
+    if (C.n <= (size_t)DIRECT_DENSE) {
+      const std::vector<double> inv = dense_inverse(tab.data(), n[0], n[1], n[2]);
+      d_dense = P->alloc<double>(inv.size());
+      HIPCHK(hipMemcpy(d_dense, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice));
+    }
+    P->direct = DirectTables{C.nx, C.ny, C.nz, d_tab, d_dense};
     for (int lt = 1; lt < L; ++lt) {
       const TailShape ts = tail_shape(*P, lt);
       if (P->dtail64 < 0 && tail_fits<double>(ts, s, true)) P->dtail64 = lt;

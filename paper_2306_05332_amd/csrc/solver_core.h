@@ -96,7 +96,7 @@ struct Plan {
   // tail's first level with it, the scratch of its multi-workgroup form and
   // the tau-steps in which the accelerated iteration surely reaches the default
   // tolerance of either precision (0: not within 200)
-  DirectTables direct{0, 0, 0, nullptr};
+  DirectTables direct{0, 0, 0, nullptr, nullptr};
   int dtail64 = -1, dtail32 = -1;
   double* dirw = nullptr;
   int steps64 = 0, steps32 = 0;

@@ -749,6 +749,13 @@ template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
                  hipStream_t st, const Batch& bt, int gs, const DirectTables* dir) {
+  // The column form takes RKL smoothing of up to four stages with the direct
+  // coarsest solve, on levels whose columns fit its threads: half the time of
+  // this kernel or less (figures in tail_col.hip).  Gauss-Seidel, more stages,
+  // a coarsest iteration and elongated levels stay here.
+  if (dir != nullptr && !gs &&
+      launch_tail_col<T>(ts, smooth, s, n_pre, n_post, periodic, b_top, u_top, stop, st, bt, *dir))
+    return;
   TailArgs<T> A;
   std::memset(&A, 0, sizeof(A));
   A.gs = gs;
