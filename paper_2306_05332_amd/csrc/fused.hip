@@ -61,11 +61,7 @@ __global__ __launch_bounds__(FNT) void k_fused_tau(LevelView<T> L, const T* __re
   const bool per = L.periodic != 0;
   const size_t sxy = (size_t)nx * ny;
 
-  // XCD-aware tile order: consecutive workgroups are dealt round-robin to the
-  // 8 XCDs, so give each XCD a contiguous run of tiles (its halos then meet
-  // in that XCD's L2).
-  int bid = blockIdx.x;
-  if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
+  const int bid = xcd_tile(blockIdx.x, nblk);
   const int tx = bid % gx_tiles;
   const int ty = (bid / gx_tiles) % gy_tiles;
   const int tz = bid / (gx_tiles * gy_tiles);
@@ -256,8 +252,7 @@ __global__ __launch_bounds__(NT) void k_tau_zq(LevelView<T> L, const T* __restri
   const int nx = L.nx, ny = L.ny, nz = L.nz;
   const bool per = L.periodic != 0;
   const size_t sxy = (size_t)nx * ny;
-  int bid = blockIdx.x;
-  if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
+  const int bid = xcd_tile(blockIdx.x, nblk);
   const int tx = bid % gx_tiles;
   const int ty = (bid / gx_tiles) % gy_tiles;
   const int tz = bid / (gx_tiles * gy_tiles);

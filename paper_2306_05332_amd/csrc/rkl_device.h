@@ -119,6 +119,17 @@ __device__ __forceinline__ void lds_poison_sync() {
 #endif
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: tile of
+// workgroup bid when every XCD gets one contiguous run of the nblk tiles, so
+// that neighbouring halos meet in one L2 (runs of nblk / 8, the first nblk % 8
+// of them one longer).  (Grids that are not a multiple of 8 ran in dealing order
+// before: a 144^3 float64 solve 2.00 -> 1.86 ms, 100^3 with Gauss-Seidel 1.35 ->
+// 1.31 ms; multiples of 8 unchanged.)
+__device__ __forceinline__ int xcd_tile(int bid, int nblk) {
+  const int x = bid & 7, q = nblk >> 3, r = nblk & 7;
+  return x * q + min(x, r) + (bid >> 3);
+}
+
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   static_assert(NT % WAVE == 0, "block size must be a multiple of the wavefront");

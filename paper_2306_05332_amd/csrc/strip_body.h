@@ -182,8 +182,7 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nx = L.nx, ny = L.ny, nz = L.nz;
   const long long sxy = (long long)nx * ny;
-  int bid = blockIdx.x;
-  if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);  // neighbouring tiles on one XCD
+  const int bid = xcd_tile(blockIdx.x, nblk);
   int tx, ty, tz;
   int xl = lane, xw = 64;  // lane within its x segment, segment width (halo lanes included)
   int yshift = 0;          // rows from the wavefront's base strip to this lane's strip

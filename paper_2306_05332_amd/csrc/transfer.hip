@@ -40,13 +40,6 @@ constexpr int RW = RBX + 2, RH = RBY + 2, RPL = RW * RH;
 constexpr int RNU = (RPL + RNT - 1) / RNT;         // haloed-plane slots per thread
 constexpr int RNI = (RBX * RBY) / RNT;             // interior slots per thread
 
-__device__ __forceinline__ int xcd_remap(int bid, int nblk) {
-  // consecutive workgroups go round-robin to the 8 XCDs: give each XCD a
-  // contiguous run of tiles so neighbouring halos meet in one L2
-  if ((nblk & 7) == 0) return (bid & 7) * (nblk >> 3) + (bid >> 3);
-  return bid;
-}
-
 template <typename TU, typename TR, bool RESTRICT, bool ADD = false>
 __global__ __launch_bounds__(RNT) void k_resid_tile(LevelView<TU> F, const TU* __restrict__ u,
                                                     const TU* __restrict__ b, TR* __restrict__ out,
@@ -79,7 +72,7 @@ __global__ __launch_bounds__(RNT) void k_resid_tile(LevelView<TU> F, const TU* _
   const int nx = F.nx, ny = F.ny, nz = F.nz;
   const bool per = F.periodic != 0;
   const size_t sxy = (size_t)nx * ny;
-  const int bid = xcd_remap(blockIdx.x, nblk);
+  const int bid = xcd_tile(blockIdx.x, nblk);
   const int tx = bid % gx_tiles, ty = (bid / gx_tiles) % gy_tiles, tzc = bid / (gx_tiles * gy_tiles);
   const int x0 = tx * RBX - 1, y0 = ty * RBY - 1;
   const int npair = (nz + 1) / 2;
@@ -278,7 +271,7 @@ __global__ __launch_bounds__(PNT) void k_prolong_tile(int fnx, int fny, int fnz,
   const int tid = threadIdx.x;
   const bool flat = fnz == 1;  // two-dimensional: one coarse plane, its own z neighbour
   const int cnx = fnx / 2, cny = fny / 2, cnz = flat ? 1 : fnz / 2;
-  const int bid = xcd_remap(blockIdx.x, nblk);
+  const int bid = xcd_tile(blockIdx.x, nblk);
   const int tx = bid % gx_tiles, ty = (bid / gx_tiles) % gy_tiles, tz = bid / (gx_tiles * gy_tiles);
   const int k0 = tz * kc, k1 = min(k0 + kc, fnz);  // kc is even
   const int cx0 = tx * (PBX / 2) - 1, cy0 = ty * (PBY / 2) - 1;
