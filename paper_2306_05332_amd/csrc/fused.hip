@@ -966,13 +966,32 @@ template <typename T>
 void launch_tau_chunk(const LevelView<T>& L, const T* u, const T* v, const T* b, T* out, T* out2, int S,
                       const StageCoef* co, hipStream_t st) {
   if (S < 1 || S > tau_chunk_max<T>(L)) fail(RKL_EINVAL, "stage chunk of unsupported length");
-  const int target = 1024;
-  switch (S) {
-    case 1: return launch_strip_ch<T, 1, 4, 4>(L, target, u, v, b, out, out2, make_fcoef<T, 1>(co), single_batch(), st);
-    case 2: return launch_strip_ch<T, 2, 4, 4>(L, target, u, v, b, out, out2, make_fcoef<T, 2>(co), single_batch(), st);
-    default:
-      if constexpr (sizeof(T) == 4)
+  if constexpr (sizeof(T) == 8) {
+    // Float64: one-wavefront four-row strips in as many z chunks as are resident
+    // together, at every size the fastest of the shapes tried (two to six rows,
+    // one or four wavefronts, chunks of 1 to 16 planes) or within 2 % of it;
+    // where two-row strips of one plane still leave SIMDs idle, those.  Us a
+    // two-stage pass, against four-row strips of four wavefronts in about 1024
+    // workgroups: 24^3 8.1 -> 6.7, 48^3 8.4 -> 8.1, 96^3 18.5 -> 14.0, 144^3
+    // 34.7 -> 27.7, 60 x 100 x 190 21.3 -> 15.5.
+    constexpr int SIMDS = 1024;
+    const bool two = strip_grid(S, 2, 1, L.nx, L.ny, L.nz, 1).per * L.nz <= SIMDS;
+    if (S == 1) {
+      if (two) return launch_strip_ch<T, 1, 2, 1>(L, 0, u, v, b, out, out2, make_fcoef<T, 1>(co), single_batch(), st);
+      return launch_strip_ch<T, 1, 4, 1>(L, 0, u, v, b, out, out2, make_fcoef<T, 1>(co), single_batch(), st);
+    }
+    if (two) return launch_strip_ch<T, 2, 2, 1>(L, 0, u, v, b, out, out2, make_fcoef<T, 2>(co), single_batch(), st);
+    return launch_strip_ch<T, 2, 4, 1>(L, 0, u, v, b, out, out2, make_fcoef<T, 2>(co), single_batch(), st);
+  } else {
+    const int target = 1024;
+    switch (S) {
+      case 1:
+        return launch_strip_ch<T, 1, 4, 4>(L, target, u, v, b, out, out2, make_fcoef<T, 1>(co), single_batch(), st);
+      case 2:
+        return launch_strip_ch<T, 2, 4, 4>(L, target, u, v, b, out, out2, make_fcoef<T, 2>(co), single_batch(), st);
+      default:
         return launch_strip_ch<T, 3, 4, 4>(L, target, u, v, b, out, out2, make_fcoef<T, 3>(co), single_batch(), st);
+    }
   }
 }
 
