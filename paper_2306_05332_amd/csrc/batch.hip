@@ -82,6 +82,7 @@ ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
   ps = std::max(ps, 2 * ew_block_count(F.n));
   ps = std::max(ps, fused_tau_blocks_max(F.nx, F.ny, F.nz));
   ps = std::max(ps, strip_rs_parts_max(F.nx, F.ny, F.nz));
+  ps = std::max(ps, (size_t)2 * BRICK_SLOTS);
   C->part_stride = (int)ps;
   C->f0 = C->alloc<double>((size_t)nb * F.n);
   C->phi = C->alloc<double>((size_t)nb * F.n);
@@ -131,13 +132,17 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   T* cur = H.u[0];
   T* alt = H.t[0];
   const Batch b0{nb, (long long)F.n, 0, CONV_INTS, ps};
+  const VBatch vb{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw};
+  const int down = level0_down<T>(P, H, nullptr, H.b[0], cur, o, nullptr, nullptr, stop, st, vb);
   int pre_done = 0;
-  if (o.n_pre > 0) {
+  if (down > 0) {
+    pre_done = o.n_pre;
+  } else if (o.n_pre > 0) {
     pre_done = relax_from_zero<T>(P, VT, F, o.n_pre, cur, alt, H.b[0], stop, st, b0, o.smoother == RKL_SMOOTH_GSRB);
   } else {
     launch_fill<T>(cur, F.n, (T)0, stop, st, b0);
   }
-  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, VBatch{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw});
+  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
   launch_add_cast<T>(C.phi, cur, F.n, stop, st, Batch{nb, (long long)F.n, (long long)F.n, CONV_INTS, 0});
   check_launch();
 }
@@ -157,14 +162,19 @@ void class_iteration_direct(ClassPlan& C, const rkl_opts& o, hipStream_t st, int
   const bool gs = o.smoother == RKL_SMOOTH_GSRB;
   const bool pair0 = o.n_pre >= 2 && pair_ok<double>(V0, o.s, gs);
   const Batch b0{nb, (long long)F.n, 0, CONV_INTS, ps};
-  double *cur = nullptr, *alt = nullptr;
-  tau_keep<double>(P, V0, bufs[ia], bufs[(ia + 1) % 3], bufs[(ia + 2) % 3], cur, alt, C.f0,
-                   pair0 ? F.smooth2 : F.smooth, C.part, stop, st, gs, b0);
-  const int nblk = (int)(gs ? gsrb_blocks<double>(V0, nb) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s, nb));
+  double *cur = bufs[(ia + 1) % 3], *alt = bufs[(ia + 2) % 3];
+  const VBatch vb{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw};
+  const int down = level0_down<double>(P, H, bufs[ia], C.f0, cur, o, C.part, nullptr, stop, st, vb);
+  int nblk = down;
+  if (down == 0) {
+    tau_keep<double>(P, V0, bufs[ia], bufs[(ia + 1) % 3], bufs[(ia + 2) % 3], cur, alt, C.f0,
+                     pair0 ? F.smooth2 : F.smooth, C.part, stop, st, gs, b0);
+    nblk = (int)(gs ? gsrb_blocks<double>(V0, nb) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s, nb));
+  }
   launch_check(C.part, nblk, 1, C.res0sq, o.tol, o.max_cycles, 1.0, C.conv, st, Batch{nb, 0, 0, 0, ps});
   check_launch();
-  vcycle_from<double>(P, H, cur, alt, C.f0, nullptr, pair0 ? 2 : 1, o, stop, st,
-                      VBatch{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw});
+  vcycle_from<double>(P, H, cur, alt, C.f0, nullptr, down > 0 ? o.n_pre : (pair0 ? 2 : 1), o, stop, st, vb, true,
+                      nullptr, down);
   for (int k = 0; k < 3; ++k)
     if (bufs[k] == cur) ia = k;
 }

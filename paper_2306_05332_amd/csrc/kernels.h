@@ -293,6 +293,21 @@ template <typename T>
 void launch_direct(const DirectTables& D, const T* b, T* u, double* W, const int* stop, hipStream_t st,
                    const Batch& bt = single_batch());
 
+// Strokes of small 3-D levels in one launch (brick.hip; RKL, even extents, no
+// face data, s steps <= 4): false or 0 when the level does not take them.
+// down: u = u0 (nullptr: the zero iterate) after `steps` tau-steps, bc =
+// R(b - M u); u distinct from u0.  Returns the workgroup count, each of which
+// writes its sum of (M u0 - b)^2 to rsum[blk] (u0 given) and of its coarse
+// values to csum[2 blk + 1], where those are not nullptr.
+// up: out = u + P e after `steps` tau-steps (out distinct from u).
+constexpr int BRICK_SLOTS = 512;  // most windows (of all members)
+template <typename T>
+int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* bc, int s, const StageCoef* co,
+                      int steps, double* rsum, double* csum, const int* stop, hipStream_t st, const Batch& bt);
+template <typename T>
+bool launch_brick_up(const LevelView<T>& L, const T* u, const T* e, const T* b, T* out, int s, const StageCoef* co,
+                     int steps, const int* stop, hipStream_t st, const Batch& bt);
+
 // Coarse tail of the V-cycle in one workgroup (tail.hip).
 constexpr int TAIL_MAX_LEVELS = 6;
 constexpr int TAIL_MAX_S = 8;

@@ -84,13 +84,19 @@ void vcycle_impl(Plan& P, const rkl_opts& o, const T* b, T* phi, double* rel_out
   const bool gs = o.smoother == RKL_SMOOTH_GSRB;
   T* home = nullptr;
   int pre_done = 0;
-  if (P.L() > 1 && o.n_post == 1 && o.n_pre >= 2 && o.n_pre % 2 == 0 && !level_is_2d(V0) &&
+  const int down = level0_down<T>(P, H, phi, b, alt, o, nullptr, P.periodic ? P.part : nullptr, nullptr, st,
+                                  VBatch{1, 0, 0, P.dscal});
+  if (down > 0) {
+    std::swap(cur, alt);
+    pre_done = o.n_pre;
+  } else if (P.L() > 1 && o.n_post == 1 && o.n_pre >= 2 && o.n_pre % 2 == 0 && !level_is_2d(V0) &&
       fused_tau_supported<T>(V0, gs ? 2 : o.s)) {
     tau_keep<T>(P, V0, phi, alt, level0_third<T>(P), cur, alt, b, P.lv[0].smooth, nullptr, nullptr, st, gs);
     pre_done = 1;
     home = phi;
   }
-  vcycle_from<T>(P, H, cur, alt, b, nullptr, pre_done, o, nullptr, st, VBatch{1, 0, 0, P.dscal}, false, home);
+  vcycle_from<T>(P, H, cur, alt, b, nullptr, pre_done, o, nullptr, st, VBatch{1, 0, 0, P.dscal}, false, home,
+                  down);
   copy_back<T>(phi, cur, P.lv[0].n, st);
   if (rel_out) {
     const double r0 = resid_norm<T>(P, V0, (const T*)nullptr, b, st);

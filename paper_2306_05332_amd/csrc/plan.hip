@@ -341,7 +341,7 @@ Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec)
   cap = std::max(cap, 2 * ew_block_count(P->lv[0].n));
   cap = std::max(cap, fused_tau_blocks_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));
   cap = std::max(cap, strip_rs_parts_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));
-  cap = std::max(cap, (size_t)1024);
+  cap = std::max(cap, (size_t)std::max(1024, 2 * BRICK_SLOTS));
   P->part = P->alloc<double>(cap);
   P->part_cap = cap;
   P->dscal = P->alloc<double>(16);

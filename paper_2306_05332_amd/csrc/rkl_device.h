@@ -119,6 +119,24 @@ __device__ __forceinline__ void lds_poison_sync() {
 #endif
 }
 
+// a b + c, rounded once.  The sweeps of a level are written with it: which of two
+// products a contraction rounds is the compiler's choice otherwise, and differs
+// between the forms of a sweep (a batch member's answer is the single solve's,
+// whichever forms the two run).
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+// 7-point M at a cell c from its six neighbours
+template <typename T>
+__device__ __forceinline__ T lap7(T c, T xm, T xp, T ym, T yp, T zm, T zp, T ihx, T ihy, T ihz) {
+  const T x = (xm + xp) - (T)2 * c, y = (ym + yp) - (T)2 * c, z = (zm + zp) - (T)2 * c;
+  return fma_of(z, ihz, fma_of(y, ihy, x * ihx));
+}
+// one RKL stage: mu y1 + nu y2 + c r
+template <typename T>
+__device__ __forceinline__ T rkl_stage(T mu, T y1, T nu, T y2, T c, T r) {
+  return fma_of(c, r, fma_of(mu, y1, nu * y2));
+}
+
 // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: tile of
 // workgroup bid when every XCD gets one contiguous run of the nblk tiles, so
 // that neighbouring halos meet in one L2 (runs of nblk / 8, the first nblk % 8

@@ -263,7 +263,20 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
       double *cur, *alt;
       int pre_done;
       int nblk, stride;
-      if (fused0) {
+      const VBatch vb{1, 0, 0, P.dscal};
+      // small grids: the whole downstroke, with the residual norm of the start
+      // state (not from the zero iterate, whose residual is f)
+      const int down =
+          cold0 && m == 0 ? 0 : level0_down<double>(P, P.h64, a, P.f0, bufs[ib], o, P.part, nullptr, stop, st, vb);
+      if (down > 0) {
+        cur = bufs[ib];
+        alt = bufs[ic];
+        nblk = down;
+        stride = 1;
+        launch_check(P.part, nblk, stride, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, st);
+        check_launch();
+        pre_done = o.n_pre;
+      } else if (fused0) {
         // first relaxation, fused with the residual norm of the start state
         tau_keep<double>(P, V0, (cold0 && m == 0) ? nullptr : a, bufs[ib], bufs[ic], cur, alt, P.f0,
                          pair0 ? F.smooth2 : F.smooth, P.part, stop, st, gs);
@@ -291,7 +304,7 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
           pre_done = 0;
         }
       }
-      vcycle_from<double>(P, P.h64, cur, alt, P.f0, nullptr, pre_done, o, stop, st, VBatch{1, 0, 0, P.dscal});
+      vcycle_from<double>(P, P.h64, cur, alt, P.f0, nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
       int ie = 0;
       for (int k = 0; k < 3; ++k)
         if (bufs[k] == cur) ie = k;
@@ -363,14 +376,19 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
       // one float32 V-cycle on M e = r from e = 0 (homogeneous level-0 ghosts)
       float* cur = P.h32.u[0];
       float* alt = P.h32.t[0];
+      const VBatch vb{1, 0, 0, P.dscal};
+      const int down =
+          level0_down<float>(P, P.h32, nullptr, P.h32.b[0], cur, o, nullptr, nullptr, stop, st, vb);  // small grids
       int pre_done = 0;
-      if (o.n_pre > 0) {
+      if (down > 0) {
+        pre_done = o.n_pre;
+      } else if (o.n_pre > 0) {
         pre_done = relax_from_zero<float>(P, V32, F, o.n_pre, cur, alt, P.h32.b[0], stop, st, single_batch(),
                                           o.smoother == RKL_SMOOTH_GSRB);
       } else {
         launch_fill<float>(cur, F.n, 0.0f, stop, st);
       }
-      vcycle_from<float>(P, P.h32, cur, alt, P.h32.b[0], nullptr, pre_done, o, stop, st, VBatch{1, 0, 0, P.dscal});
+      vcycle_from<float>(P, P.h32, cur, alt, P.h32.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
       if (fold) eprev = cur;  // read by the next iteration's defect pass, before its V-cycle runs
       else launch_add_cast<float>(phi, cur, F.n, stop, st);
       check_launch();

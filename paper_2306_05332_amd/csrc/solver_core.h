@@ -485,6 +485,22 @@ struct VBatch {
   double* dirw = nullptr;  // direct coarsest solve's scratch (nullptr: the plan's own)
 };
 
+// Level 0's downstroke in one launch where the level is small enough: u0
+// (nullptr: the zero iterate) -> u, and H.b[1]; rsum and csum as
+// launch_brick_down.  Returns the workgroup count, 0 when not taken.
+template <typename T>
+int level0_down(Plan& P, Hier<T>& H, const T* u0, const T* b, T* u, const rkl_opts& o, double* rsum, double* csum,
+                const int* stop, hipStream_t st, const VBatch& vb) {
+  if (P.L() < 2 || o.smoother == RKL_SMOOTH_GSRB || !(o.fuse & 2) || !direct_coarse<T>(P, o)) return 0;
+  const Lev& F = P.lv[0];
+  const int n = launch_brick_down<T>(view<T>(F, P.periodic, nullptr), u0, b, u, H.b[1], (int)F.smooth.size(),
+                                     F.smooth.data(), o.n_pre, rsum, csum, stop, st,
+                                     Batch{vb.nb, (long long)F.n, (long long)P.lv[1].n, vb.stop_stride,
+                                           vb.part_stride});
+  if (n > 0) check_launch();
+  return n;
+}
+
 //
 // Periodic compatibility (Sec. 2.3): the restricted residual of a mean-free
 // right-hand side is mean-free up to rounding, since the periodic M sums to
@@ -498,13 +514,15 @@ struct VBatch {
 // sees the mean, removes it there.  (A removal on every level took 19 us of
 // the 470 us cycle at 256^3 float64.)
 //
+// restricted > 0: level 0's downstroke is done, its restriction's partial pairs
+// counted (level0_down).
 // home (optional): the array that the last level-0 relaxation writes, neither
 // cur0 nor read by it; for n_post = 1 and a level whose relaxations are single
 // passes.
 template <typename T>
 void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const double* faces0, int pre_done,
                  const rkl_opts& o, const int* stop, hipStream_t st, const VBatch& vb, bool mean_free = true,
-                 T* home = nullptr) {
+                 T* home = nullptr, int restricted = 0) {
   const int L = P.L();
   double* part = vb.part ? vb.part : P.part;
   auto V = [&](int l) { return view<T>(P.lv[l], P.periodic, l == 0 ? faces0 : nullptr); };
@@ -527,8 +545,10 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
   const int lbot = lt > 0 ? lt : L - 1;
   const bool fuse_rs = (o.fuse & 2) != 0;
   // pairs of partial sums the fused restriction into the next level wrote (0: restrict separately)
-  int rs_pairs = relax_restrict<T>(P, V(0), P.lv[0], std::max(0, o.n_pre - pre_done), cur0, alt0, b0, H.b[1], part,
-                                   stop, st, B1(0), B2(0, 1), gs, fuse_rs);
+  int rs_pairs = restricted;
+  if (!restricted)
+    rs_pairs = relax_restrict<T>(P, V(0), P.lv[0], std::max(0, o.n_pre - pre_done), cur0, alt0, b0, H.b[1], part, stop,
+                                 st, B1(0), B2(0, 1), gs, fuse_rs);
   for (int l = 1; l <= lbot; ++l) {
     T* fu = (l == 1) ? cur0 : H.u[l - 1];
     const T* fb = (l == 1) ? b0 : H.b[l - 1];
@@ -558,7 +578,14 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
       check_launch();
     }
     if (l < L - 1) {  // then l + 1 <= lbot: the loop restricts this level next
-      if (o.n_pre > 0) {
+      // small levels: the whole stroke in one launch (rs_pairs: restricted; the
+      // sums are not needed with a direct coarsest solve)
+      if (direct && !gs && fuse_rs &&
+          launch_brick_down<T>(V(l), nullptr, H.b[l], H.u[l], H.b[l + 1], (int)C.smooth.size(), C.smooth.data(),
+                               o.n_pre, nullptr, nullptr, stop, st, B2(l, l + 1)) > 0) {
+        check_launch();
+        rs_pairs = 1;
+      } else if (o.n_pre > 0) {
         const int done = relax_from_zero<T>(P, V(l), C, o.n_pre, H.u[l], H.t[l], H.b[l], stop, st, B1(l), gs);
         rs_pairs = relax_restrict<T>(P, V(l), C, o.n_pre - done, H.u[l], H.t[l], H.b[l], H.b[l + 1], part, stop, st,
                                      B1(l), B2(l, l + 1), gs, fuse_rs);
@@ -581,6 +608,13 @@ void vcycle_from(Plan& P, Hier<T>& H, T*& cur0, T*& alt0, const T* b0, const dou
     const Lev& F = P.lv[l];
     // prolongation + correction (Sec. 2.1 steps 4-5) fused into the first
     // post-smoothing tau-step where the level's strip kernel allows it
+    if (!gs && (o.fuse & 1) &&
+        launch_brick_up<T>(V(l), cu, H.u[l + 1], bl, ca, (int)F.smooth.size(), F.smooth.data(), o.n_post, stop, st,
+                           B2(l, l + 1))) {
+      check_launch();
+      std::swap(cu, ca);
+      continue;
+    }
     if (o.n_post > 0 && !gs && (o.fuse & 1) &&
         launch_fused_tau_pro<T>(V(l), cu, H.u[l + 1], bl, ca, (int)F.smooth.size(), F.smooth.data(), stop, st,
                                 B2(l, l + 1))) {

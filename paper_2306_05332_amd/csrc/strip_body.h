@@ -396,13 +396,8 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
     }
     return sz;
   };
-  // 3 a + b, rounded once: explicit, so that a chunk's first planes and its
-  // march, compiled apart, give the same bits wherever the chunks are cut
-  // (a batch member's answer is the single solve's)
-  auto fma3 = [](T a, T b) -> T {
-    if constexpr (sizeof(T) == 8) return __builtin_fma(3.0, a, b);
-    else return __builtin_fmaf(3.0f, a, b);
-  };
+  // 3 a + b, rounded once
+  auto fma3 = [](T a, T b) -> T { return fma_of((T)3, a, b); };
   // PRO: E[i] = 64 x (coarse plane C interpolated in x and y onto held row i),
   // ghost signs included (x, then y, as eq. prolongation_example_3D weighs)
   auto cfin = [&](const T(&C)[PRO && !PDMA ? NC : 1][2], T sz, T(&E)[PRO ? NU : 1]) {
@@ -534,8 +529,7 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
         if (p == 0) zm = -c;
         if (p == nz - 1) zp = -c;
       }
-      return ((xm + xp) - (T)2 * c) * L.ihx2 + ((ym + yp) - (T)2 * c) * L.ihy2 +
-             ((zm + zp) - (T)2 * c) * L.ihz2;
+      return lap7(c, xm, xp, ym, yp, zm, zp, L.ihx2, L.ihy2, L.ihz2);
     }
   };
 
@@ -697,10 +691,8 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
                 zp1 = -c1;
               }
             }
-            const T l0 = ((xm0 + xp0) - (T)2 * c0) * L.ihx2 + ((ym + c1) - (T)2 * c0) * L.ihy2 +
-                         ((zm0 + zp0) - (T)2 * c0) * L.ihz2;
-            const T l1 = ((xm1 + xp1) - (T)2 * c1) * L.ihx2 + ((c0 + yp) - (T)2 * c1) * L.ihy2 +
-                         ((zm1 + zp1) - (T)2 * c1) * L.ihz2;
+            const T l0 = lap7(c0, xm0, xp0, ym, c1, zm0, zp0, L.ihx2, L.ihy2, L.ihz2);
+            const T l1 = lap7(c1, xm1, xp1, c0, yp, zm1, zp1, L.ihx2, L.ihy2, L.ihz2);
             const T r0 = BR[k][0] - l0, r1 = BR[k][1] - l1;
             const bool ok = xown && ga < ny;
             if (ok) rs2 += (double)r0 * (double)r0 + (double)r1 * (double)r1;
@@ -766,8 +758,8 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
             y = U1[i] + gscoef(co.c[0], i, p) * res;
             if ((xpar(i) ^ ((rodd >> i) & 1) ^ zodd(p)) != 0) y = U1[i];  // black cell: unchanged
           } else {
-            if constexpr (CH) y = co.mu[0] * U1[i] + co.nu[0] * Vc[i] + co.c[0] * res;
-            else y = U1[i] + co.c[0] * res;
+            if constexpr (CH) y = rkl_stage(co.mu[0], U1[i], co.nu[0], Vc[i], co.c[0], res);
+            else y = fma_of(co.c[0], res, U1[i]);
           }
           if (part != nullptr && pown && i >= HY && i < HY + R && own(i) && ((rin >> i) & 1u))
             r2 += (double)res * (double)res;
@@ -796,7 +788,7 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
             y = Xc[i] + gscoef(co.c[j - 1], i, p) * res;
             if ((xpar(i) ^ ((rodd >> i) & 1) ^ zodd(p)) == 0) y = Xc[i];  // red cell: unchanged
           } else {
-            y = co.mu[j - 1] * Xc[i] + co.nu[j - 1] * y2 + co.c[j - 1] * res;
+            y = rkl_stage(co.mu[j - 1], Xc[i], co.nu[j - 1], y2, co.c[j - 1], res);
           }
           if (j == S) YS[i] = y;
           else Yq[j - 1][2][i] = y;
