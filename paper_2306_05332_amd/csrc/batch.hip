@@ -83,6 +83,7 @@ ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
   ps = std::max(ps, fused_tau_blocks_max(F.nx, F.ny, F.nz));
   ps = std::max(ps, strip_rs_parts_max(F.nx, F.ny, F.nz));
   ps = std::max(ps, (size_t)2 * BRICK_SLOTS);
+  if (F.nz == 1) ps = std::max(ps, 2 * win2_blocks_max(F.nx, F.ny));
   C->part_stride = (int)ps;
   C->f0 = C->alloc<double>((size_t)nb * F.n);
   C->phi = C->alloc<double>((size_t)nb * F.n);

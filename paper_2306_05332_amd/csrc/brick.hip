@@ -413,7 +413,6 @@ static bool brick_args(BrickArgs<T>& A, const LevelView<T>& L, int s, const Stag
 template <typename T>
 static int brick_len(BrickArgs<T>& A, const LevelView<T>& L, int s, const StageCoef* co, int steps, int halo, int nb,
                      int most) {
-  if (level_is_2d(L)) return 0;
   for (int limit = BRICK_SLOTS / 2; limit <= most; limit *= 2)
     for (int len : {4, 6}) {
       if (!brick_args(A, L, s, co, steps, halo, len)) return 0;
@@ -425,6 +424,7 @@ static int brick_len(BrickArgs<T>& A, const LevelView<T>& L, int s, const StageC
 template <typename T>
 int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* bc, int s, const StageCoef* co,
                       int steps, double* rsum, double* csum, const int* stop, hipStream_t st, const Batch& bt) {
+  if (level_is_2d(L)) return launch_win2_down<T>(L, u0, b, u, bc, s, co, steps, rsum, csum, stop, st, bt);
   BrickArgs<T> A;
   const bool zero = u0 == nullptr;
   const int len = brick_len(A, L, s, co, steps, s * steps + (zero ? 0 : 1), bt.nb,
@@ -445,6 +445,7 @@ int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* b
 template <typename T>
 bool launch_brick_up(const LevelView<T>& L, const T* u, const T* e, const T* b, T* out, int s, const StageCoef* co,
                      int steps, const int* stop, hipStream_t st, const Batch& bt) {
+  if (level_is_2d(L)) return launch_win2_up<T>(L, u, e, b, out, s, co, steps, stop, st, bt) > 0;
   BrickArgs<T> A;
   const int len = brick_len(A, L, s, co, steps, (s * steps + 1) & ~1, bt.nb, BRICK_SLOTS);
   if (len == 0) return false;

@@ -304,6 +304,16 @@ constexpr int BRICK_SLOTS = 512;  // most windows (of all members)
 template <typename T>
 int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* bc, int s, const StageCoef* co,
                       int steps, double* rsum, double* csum, const int* stop, hipStream_t st, const Batch& bt);
+// the same strokes of a two-dimensional level of any size (window2d.hip), which
+// the brick launchers hand on; 0 when not taken
+template <typename T>
+int launch_win2_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* bc, int s, const StageCoef* co,
+                     int steps, double* rsum, double* csum, const int* stop, hipStream_t st, const Batch& bt);
+template <typename T>
+int launch_win2_up(const LevelView<T>& L, const T* u, const T* e, const T* b, T* out, int s, const StageCoef* co,
+                   int steps, const int* stop, hipStream_t st, const Batch& bt);
+// bound on win2's workgroups for a level
+size_t win2_blocks_max(int nx, int ny);
 template <typename T>
 bool launch_brick_up(const LevelView<T>& L, const T* u, const T* e, const T* b, T* out, int s, const StageCoef* co,
                      int steps, const int* stop, hipStream_t st, const Batch& bt);

@@ -342,6 +342,7 @@ Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec)
   cap = std::max(cap, fused_tau_blocks_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));
   cap = std::max(cap, strip_rs_parts_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));
   cap = std::max(cap, (size_t)std::max(1024, 2 * BRICK_SLOTS));
+  if (P->lv[0].nz == 1) cap = std::max(cap, 2 * win2_blocks_max(P->lv[0].nx, P->lv[0].ny));
   P->part = P->alloc<double>(cap);
   P->part_cap = cap;
   P->dscal = P->alloc<double>(16);
