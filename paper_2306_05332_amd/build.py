@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "librklpoisson.so")
 ARCH = os.environ.get("RKL_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["strip.hip", "strip_forms64.hip", "strip_forms32.hip", "strip_rs.hip", "kernels.hip", "transfer.hip",
-           "coarse.hip", "direct.hip", "tail.hip", "tail_col.hip", "brick.hip", "window2d.hip", "fused.hip", "plan.hip",
+           "defect.hip", "coarse.hip", "direct.hip", "tail.hip", "tail_col.hip", "brick.hip", "window2d.hip", "fused.hip", "plan.hip",
            "solve.hip", "batch.hip", "tune.hip", "levels.hip", "noalloc.hip"]
 
 HIPCC_FLAGS = [

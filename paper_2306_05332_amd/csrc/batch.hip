@@ -78,7 +78,7 @@ ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
   C->nb = nb;
   const Lev& F = base.lv[0];
   const int L = base.L();
-  size_t ps = 2 * resid_blocks(F.nx, F.ny, F.nz);
+  size_t ps = 2 * std::max(resid_blocks(F.nx, F.ny, F.nz), defect_blocks(F.nx, F.ny, F.nz));
   ps = std::max(ps, 2 * ew_block_count(F.n));
   ps = std::max(ps, fused_tau_blocks_max(F.nx, F.ny, F.nz));
   ps = std::max(ps, strip_rs_parts_max(F.nx, F.ny, F.nz));
@@ -127,7 +127,7 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   const LevelView<double> V0 = view<double>(F, P.periodic, nullptr);
   const LevelView<T> VT = view<T>(F, P.periodic, nullptr);
   launch_residual<double, T>(V0, C.phi, C.f0, H.b[0], C.part, stop, st, Batch{nb, (long long)F.n, 0, CONV_INTS, ps});
-  launch_check(C.part, (int)resid_blocks(F.nx, F.ny, F.nz), 2, C.res0sq, o.tol, o.max_cycles, (double)F.n, C.conv,
+  launch_check(C.part, (int)defect_blocks(F.nx, F.ny, F.nz, nb), 2, C.res0sq, o.tol, o.max_cycles, (double)F.n, C.conv,
                st, Batch{nb, 0, 0, 0, ps});
   check_launch();  // periodic: no level-0 mean pass (the defect is mean-free up to rounding; see solve_mixed)
   T* cur = H.u[0];

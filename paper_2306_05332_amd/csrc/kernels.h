@@ -8,7 +8,8 @@
 namespace rkl {
 
 size_t stencil_blocks(int nx, int ny, int nz);  // blocks of the per-stage kernel
-size_t resid_blocks(int nx, int ny, int nz);    // partial-sum pairs written by residual-type kernels
+size_t resid_blocks(int nx, int ny, int nz);    // partial-sum pairs written by launch_resid_restrict
+size_t defect_blocks(int nx, int ny, int nz, int nb = 1);  // by launch_residual(_add) on nb members (most: nb = 1)
 size_t ew_block_count(size_t n);                // partial-sum slots used by k_scale / k_sum
 
 // Device-side state of the V-cycle convergence loop.
@@ -29,10 +30,13 @@ struct ConvState {
 template <typename T>
 void launch_stage(const LevelView<T>& L, const T* yp, const T* ypp, const T* b, T* yout, double mu,
                   double nu, double c, int first, const int* stop, hipStream_t st);
-// transfer.hip: part receives resid_blocks() pairs (sum r^2, sum r | sum of coarse values)
+// transfer.hip (3-D: defect.hip): part receives defect_blocks() pairs (sum r^2, sum r)
 template <typename TU, typename TR>
 void launch_residual(const LevelView<TU>& L, const TU* u, const TU* b, TR* r_out, double* part,
                      const int* stop, hipStream_t st, const Batch& bt = single_batch());
+template <typename TU, typename TR>
+void launch_defect_3d(const LevelView<TU>& L, const TU* u, const TU* b, TR* r_out, double* part, const int* stop,
+                      hipStream_t st, const Batch& bt);
 // u_out = u + e and r_out = b - M u_out in one pass (float64 u, float32 e;
 // 3-D levels, one grid, u_out distinct from u); part as launch_residual
 void launch_residual_add(const LevelView<double>& L, const double* u, const float* e, const double* b,

@@ -110,7 +110,7 @@ void vcycle_impl(Plan& P, const rkl_opts& o, const T* b, T* phi, double* rel_out
 template <typename T>
 double residual_impl(Plan& P, const LevelView<T>& V, const T* b, const T* u, T* r_out, hipStream_t st) {
   launch_residual<T, T>(V, u, b, r_out, P.part, nullptr, st);
-  launch_reduce(P.part, (int)resid_blocks(V.nx, V.ny, V.nz), 2, 1, P.dscal, nullptr, st);
+  launch_reduce(P.part, (int)defect_blocks(V.nx, V.ny, V.nz), 2, 1, P.dscal, nullptr, st);
   check_launch();
   return std::sqrt(readback(P, 1, st)[0]);
 }

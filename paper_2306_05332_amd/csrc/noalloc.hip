@@ -27,7 +27,7 @@
 namespace rkl {
 
 // Partial-sum pairs the residual kernels of one call may write.  A 3-D
-// residual workgroup covers a 64 x 16 tile over up to 16 planes, so 65536
+// residual workgroup covers 64 x 16 columns over up to 16 planes, so 65536
 // pairs cover grids up to 1024^3 cells; 2-D grids take one pair per
 // workgroup of their row-pair chunks.
 constexpr size_t NOALLOC_MAX_PAIRS = 65536;
@@ -75,7 +75,7 @@ extern "C" rkl_status rkl_residual_noalloc(const rkl_grid* grid, const double* f
   return guarded([&]() -> rkl_status {
     validate_grid(grid, bc_faces);
     if (!f || !phi) fail(RKL_EINVAL, "f and phi must be non-NULL");
-    const size_t pairs = resid_blocks(grid->nx, grid->ny, grid->nz);
+    const size_t pairs = defect_blocks(grid->nx, grid->ny, grid->nz);
     if (pairs > NOALLOC_MAX_PAIRS)
       fail(RKL_EINVAL, "grid needs " + std::to_string(pairs) + " partial-sum pairs; the no-allocation residual "
                        "holds at most " + std::to_string(NOALLOC_MAX_PAIRS) + " (about 1024^3 cells in 3-D)");

@@ -337,7 +337,7 @@ Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec)
   }
   // partial sums: residual kernels (pairs), fused tau-step (one per block), elementwise
   // sums (pairs for the source scaling)
-  size_t cap = 2 * resid_blocks(g.nx, g.ny, g.nz);
+  size_t cap = 2 * std::max(resid_blocks(g.nx, g.ny, g.nz), defect_blocks(g.nx, g.ny, g.nz));
   cap = std::max(cap, 2 * ew_block_count(P->lv[0].n));
   cap = std::max(cap, fused_tau_blocks_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));
   cap = std::max(cap, strip_rs_parts_max(P->lv[0].nx, P->lv[0].ny, P->lv[0].nz));

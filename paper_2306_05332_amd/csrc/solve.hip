@@ -287,7 +287,7 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
         pre_done = pair0 ? 2 : 1;
       } else {
         launch_residual<double, double>(V0, a, P.f0, (double*)nullptr, P.part, stop, st);
-        nblk = (int)resid_blocks(F.nx, F.ny, F.nz);
+        nblk = (int)defect_blocks(F.nx, F.ny, F.nz);
         stride = 2;
         launch_check(P.part, nblk, stride, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, st);
         check_launch();
@@ -348,7 +348,7 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
     check_launch();
   }
   const int* stop = &P.dconv->stop;  // the state was reset by solve_start
-  const int nblk = (int)resid_blocks(F.nx, F.ny, F.nz);
+  const int nblk = (int)defect_blocks(F.nx, F.ny, F.nz);
   // When phi and e together overflow the last-level cache, the update
   // phi += e of an iteration is folded into the next iteration's defect pass
   // (launch_residual_add), which writes the updated phi into the other one

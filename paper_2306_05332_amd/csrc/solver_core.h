@@ -158,7 +158,7 @@ template <typename T>
 void resid_norm2_async(Plan& P, const LevelView<T>& V, const T* u, const T* b, hipStream_t st, int at = 0) {
   launch_residual<T, T>(V, u, b, (T*)nullptr, P.part, nullptr, st);
   check_launch();
-  launch_reduce(P.part, (int)resid_blocks(V.nx, V.ny, V.nz), 2, 1, P.dscal + at, nullptr, st);
+  launch_reduce(P.part, (int)defect_blocks(V.nx, V.ny, V.nz), 2, 1, P.dscal + at, nullptr, st);
   check_launch();
 }
 

@@ -1,13 +1,7 @@
-// LDS-tiled residual, residual + restriction, and prolongation + correction.
+// LDS-tiled residual + restriction, and prolongation + correction (the plain
+// residual of a 3-D level: defect.hip).
 //
-//   k_resid_tile<.., false>  r = b - M u (Sec. 2.1 eq. residual, opposite sign)
-//                            with float64 partial sums of r^2 and r
-//   k_resid_tile<.., false, true>  the same for u' = u + e (e float32), which
-//                            it also writes: the mixed path's update of the
-//                            float64 iterate folded into the next defect
-//                            (Sec. 2.2.3), 32 bytes a cell against 20 + 20
-//                            for the update and the defect apart
-//   k_resid_tile<.., true>   b_{l+1} = R(b_l - M_l u_l): the 8-child average of
+//   k_resid_tile             b_{l+1} = R(b_l - M_l u_l): the 8-child average of
 //                            eq. restriction_example_3D applied to the residual
 //                            (Sec. 2.1 steps 2a/2b), with float64 partials of
 //                            the fine r^2 and of the coarse values (the latter
@@ -23,8 +17,8 @@
 // weights into the (9, 3, 3, 1)/16 of eq. prolongation_example_2D
 // (27 + 9 = 36, 9 + 3 = 12, 3 + 1 = 4 sixty-fourths).
 //
-// Both march upward in z.  The residual kernels keep four fine u planes of a
-// 64 x 16 tile (plus a one-cell halo) in an LDS ring and handle one coarse
+// Both march upward in z.  The residual kernel keeps four fine u planes of a
+// 64 x 16 tile (plus a one-cell halo) in an LDS ring and handles one coarse
 // plane (two fine planes) per step; the prolongation keeps three coarse
 // planes of the tile's coarse footprint in LDS.  The next planes are loaded
 // into registers while the current ones are processed, so each HBM word is
@@ -40,31 +34,25 @@ constexpr int RW = RBX + 2, RH = RBY + 2, RPL = RW * RH;
 constexpr int RNU = (RPL + RNT - 1) / RNT;         // haloed-plane slots per thread
 constexpr int RNI = (RBX * RBY) / RNT;             // interior slots per thread
 
-template <typename TU, typename TR, bool RESTRICT, bool ADD = false>
+template <typename TU>
 __global__ __launch_bounds__(RNT) void k_resid_tile(LevelView<TU> F, const TU* __restrict__ u,
-                                                    const TU* __restrict__ b, TR* __restrict__ out,
+                                                    const TU* __restrict__ b, TU* __restrict__ out,
                                                     int kc, int gx_tiles, int gy_tiles, int nblk,
                                                     double* __restrict__ part, Batch bt,
-                                                    const int* __restrict__ stop, const float* __restrict__ e,
-                                                    TU* __restrict__ unew) {
-  static_assert(!ADD || !RESTRICT, "the update is folded into the plain defect only");
+                                                    const int* __restrict__ stop) {
   {
     const long long mb = blockIdx.y;
-    if (u != nullptr) u += mb * bt.s0;
-    if (ADD) {
-      e += mb * bt.s0;
-      unew += mb * bt.s0;
-    }
+    u += mb * bt.s0;
     b += mb * bt.s0;
-    if (out != nullptr) out += mb * (RESTRICT ? bt.s1 : bt.s0);
+    out += mb * bt.s1;
     part += mb * bt.part_stride;
     if (stop != nullptr) stop += mb * bt.stop_stride;
   }
   __shared__ TU ring[4][RPL];
-  __shared__ TU zs[RESTRICT ? RBY : 1][RESTRICT ? RBX : 1];
+  __shared__ TU zs[RBY][RBX];
   __shared__ double red[RNT / WAVE];
   lds_poison(&ring[0][0], 4 * RPL);
-  lds_poison(&zs[0][0], (RESTRICT ? RBY : 1) * (RESTRICT ? RBX : 1));
+  lds_poison(&zs[0][0], RBY * RBX);
   lds_poison(red, RNT / WAVE);
   lds_poison_sync();
   if (stop != nullptr && *stop) return;
@@ -109,13 +97,10 @@ __global__ __launch_bounds__(RNT) void k_resid_tile(LevelView<TU> F, const TU* _
   TU pa[RNU], pb[RNU];   // u planes in flight
   TU ba[RNI], bb[RNI];   // b planes in flight
   auto load_u = [&](int p, TU (&dst)[RNU]) {
-    const bool ok = u != nullptr && plane_ok(p) && (per || p < nz);
+    const bool ok = plane_ok(p) && (per || p < nz);
     const size_t zo = ok ? (size_t)zw(p) * sxy : 0;
 #pragma unroll
-    for (int q = 0; q < RNU; ++q) {
-      dst[q] = (ok && goff[q] >= 0) ? u[zo + goff[q]] : (TU)0;
-      if (ADD && ok && goff[q] >= 0) dst[q] += (TU)e[zo + goff[q]];
-    }
+    for (int q = 0; q < RNU; ++q) dst[q] = (ok && goff[q] >= 0) ? u[zo + goff[q]] : (TU)0;
   };
   auto load_b = [&](int p, TU (&dst)[RNI]) {
     const bool ok = p >= 0 && p < nz;
@@ -196,46 +181,21 @@ __global__ __launch_bounds__(RNT) void k_resid_tile(LevelView<TU> F, const TU* _
             r1 = resid(q, p1, bc1[q]);
             s2 += (double)r1 * (double)r1;
           }
-          if (!RESTRICT) {
-            s1 += (double)r0 + (double)r1;
-            if (ADD) {
-              // u' of the cell, as the ring holds it, and r: non-temporal
-              // hints (the form runs on levels beyond the last-level cache,
-              // where neither is read again before it would be evicted;
-              // 512^3 mixed solve 31.35 -> 30.78 ms)
-              const int idx = tid + q * RNT;
-              const int o = (idx / RBX + 1) * RW + (idx % RBX + 1);
-              const size_t c0 = (size_t)p0 * sxy + (size_t)igy[q] * nx + igx[q];
-              __builtin_nontemporal_store((TR)r0, out + c0);
-              __builtin_nontemporal_store(ring[rslot(p0)][o], unew + c0);
-              if (has1) {
-                __builtin_nontemporal_store((TR)r1, out + c0 + sxy);
-                __builtin_nontemporal_store(ring[rslot(p1)][o], unew + c0 + sxy);
-              }
-            } else if (out != nullptr) {
-              out[(size_t)p0 * sxy + (size_t)igy[q] * nx + igx[q]] = (TR)r0;
-              if (has1) out[(size_t)p1 * sxy + (size_t)igy[q] * nx + igx[q]] = (TR)r1;
-            }
-          }
         }
-        if (RESTRICT) {
-          const int idx = tid + q * RNT;
-          zs[RESTRICT ? idx / RBX : 0][RESTRICT ? idx % RBX : 0] = r0 + r1;
-        }
+        const int idx = tid + q * RNT;
+        zs[idx / RBX][idx % RBX] = r0 + r1;
       }
       __syncthreads();
-      if (RESTRICT) {
-        const int cx = tid % (RBX / 2), cy = tid / (RBX / 2);  // 32 x 8 coarse cells, one per thread
-        const int cnx = nx / 2, cny = ny / 2;
-        const int gcx = tx * (RBX / 2) + cx, gcy = ty * (RBY / 2) + cy;
-        if (gcx < cnx && gcy < cny) {
-          const TU v = ((zs[2 * cy][2 * cx] + zs[2 * cy][2 * cx + 1]) +
-                        (zs[2 * cy + 1][2 * cx] + zs[2 * cy + 1][2 * cx + 1])) * (nz == 1 ? (TU)0.25 : (TU)0.125);
-          out[((size_t)K * cny + gcy) * cnx + gcx] = (TR)v;
-          s1 += (double)v;
-        }
-        __syncthreads();
+      const int cx = tid % (RBX / 2), cy = tid / (RBX / 2);  // 32 x 8 coarse cells, one per thread
+      const int cnx = nx / 2, cny = ny / 2;
+      const int gcx = tx * (RBX / 2) + cx, gcy = ty * (RBY / 2) + cy;
+      if (gcx < cnx && gcy < cny) {
+        const TU v = ((zs[2 * cy][2 * cx] + zs[2 * cy][2 * cx + 1]) +
+                      (zs[2 * cy + 1][2 * cx] + zs[2 * cy + 1][2 * cx + 1])) * (nz == 1 ? (TU)0.25 : (TU)0.125);
+        out[((size_t)K * cny + gcy) * cnx + gcx] = v;
+        s1 += (double)v;
       }
+      __syncthreads();
     }
   }
   const double t2 = block_sum<RNT>(s2, red);
@@ -662,20 +622,7 @@ void launch_residual(const LevelView<TU>& L, const TU* u, const TU* b, TR* r_out
                        g.jc, g.gx, part, bt, stop);
     return;
   }
-  const TileGrid g = resid_grid(L.nx, L.ny, L.nz);
-  hipLaunchKernelGGL((k_resid_tile<TU, TR, false>), dim3(g.nblk, bt.nb), dim3(RNT), 0, st, L, u, b, r_out,
-                     g.kc, g.gx, g.gy, g.nblk, part, bt, stop, (const float*)nullptr, (TU*)nullptr);
-}
-
-void launch_residual_add(const LevelView<double>& L, const double* u, const float* e, const double* b,
-                         double* u_out, float* r_out, double* part, const int* stop, hipStream_t st) {
-  if (L.nz == 1) fail(RKL_EINVAL, "the folded update is built for 3-D levels");
-  if (u == nullptr || e == nullptr || u_out == nullptr || r_out == nullptr || u_out == u)
-    fail(RKL_EINVAL, "folded update: bad buffers");
-  const TileGrid g = resid_grid(L.nx, L.ny, L.nz);
-  const Batch bt = single_batch();
-  hipLaunchKernelGGL((k_resid_tile<double, float, false, true>), dim3(g.nblk, 1), dim3(RNT), 0, st, L, u, b, r_out,
-                     g.kc, g.gx, g.gy, g.nblk, part, bt, stop, e, u_out);
+  launch_defect_3d<TU, TR>(L, u, b, r_out, part, stop, st, bt);
 }
 
 template <typename T>
@@ -688,8 +635,8 @@ void launch_resid_restrict(const LevelView<T>& F, const T* u, const T* b, T* bc,
     return;
   }
   const TileGrid g = resid_grid(F.nx, F.ny, F.nz);
-  hipLaunchKernelGGL((k_resid_tile<T, T, true>), dim3(g.nblk, bt.nb), dim3(RNT), 0, st, F, u, b, bc, g.kc,
-                     g.gx, g.gy, g.nblk, part, bt, stop, (const float*)nullptr, (T*)nullptr);
+  hipLaunchKernelGGL(k_resid_tile<T>, dim3(g.nblk, bt.nb), dim3(RNT), 0, st, F, u, b, bc, g.kc, g.gx, g.gy, g.nblk,
+                     part, bt, stop);
 }
 
 template <typename T>
