@@ -237,7 +237,8 @@ void launch_strip_ch(const LevelView<T>& L, int target, const T* u, const T* v, 
 // (strip_rs.hip); returns the workgroup count (partial pairs written).
 // Stacked strips of R WY - 2 >= RS_MIN_ROWS output rows, even extents.
 constexpr int RS_MIN_ROWS = 14;
-StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target);
+// over: planes per chunk where `target` workgroups would take more than 64
+StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target, int over);
 template <typename T, int S, int R, int WY, bool SHY>
 int launch_strip_rs(const LevelView<T>& L, int target, const T* u, const T* b, T* out, T* bc, const FCoef<T, S>& fc,
                     double* part, const int* stop, const Batch& bt, hipStream_t st);

@@ -37,10 +37,17 @@ template <typename T, int S, int R, int WY, bool PER, bool SHY, bool NT>
 static void launch_strip_pro_k(const LevelView<T>& L, int target, const T* u, const T* e, const T* b, T* out,
                                const FCoef<T, S>& fc, const int* stop, const Batch& bt, hipStream_t st) {
   auto kern = k_tau_strip_pro<T, S, R, WY, PER, SHY, NT>;
-  if (target <= 0) {
-    static std::atomic<int> slots[64];
-    const int per = strip_grid(S, R, WY, L.nx, L.ny, L.nz, 1, false, false).per;
-    target = std::max(1, resident_wgs(kern, 64 * WY, slots) / (per * bt.nb)) * per;
+  static std::atomic<int> slots[64];
+  const int per = strip_grid(S, R, WY, L.nx, L.ny, L.nz, 1, false, false).per;
+  if (target <= 0) target = std::max(1, resident_wgs(kern, 64 * WY, slots) / (per * bt.nb)) * per;
+  // A tuned target is the plain tau-step's.  Here a chunk's first planes cost the
+  // coarse planes around them as well, so float32 levels large enough to fill the
+  // device twice with chunks of 32 planes take no shorter ones (512^3 cycle in
+  // chunks of 9 planes, as tuned, and of 32: 1664 and 1610 us periodic, 1888 and
+  // 1775 Dirichlet; float64 prefers its tuned chunks).
+  if (sizeof(T) == 4) {
+    const int most = per * ((L.nz + 31) / 32);
+    if (target > most && (long long)most * bt.nb >= 2ll * resident_wgs(kern, 64 * WY, slots)) target = most;
   }
   const StripGrid g = strip_grid(S, R, WY, L.nx, L.ny, L.nz, target, false, false);
   hipLaunchKernelGGL(kern, dim3(g.nblk, bt.nb), dim3(64 * WY), 0, st, L, u, e, b, out, fc, g.zc, g.gx, g.gy, g.nblk,

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(64 * WY, (strip_min_waves<T, R, WY>())) void k_tau_
 // them); the z chunks are as many as
 // fit in one such wave of workgroups, since a partial second wave would cost
 // nearly a whole pass
-StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target) {
+StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target, int over) {
   StripGrid g;
   g.ox = 64 - 2 * (s + 1);
   g.map = StripMap{0, 0, 0, 0, 0};
@@ -42,7 +42,8 @@ StripGrid strip_grid_rs(int s, int R, int WY, int nx, int ny, int nz, int target
   g.gy = (ny + R * WY - 3) / (R * WY - 2);
   g.per = g.gx * g.gy;
   const int chunks = std::max(1, target / g.per);
-  int zc = std::max(2, std::min(64, (nz + chunks - 1) / chunks));
+  int zc = std::max(2, (nz + chunks - 1) / chunks);
+  if (zc > 64) zc = over;
   zc += zc & 1;
   g.zc = zc;
   g.gz = (nz + zc - 1) / zc;
@@ -60,8 +61,13 @@ static int launch_rs_k(const LevelView<T>& L, const T* u, const T* b, T* out, T*
                        double* part, const int* stop, const Batch& bt, hipStream_t st) {
   static std::atomic<int> slots[64];
   auto kern = k_tau_strip_rs<T, S, R, WY, PER, SHY, NT>;
+  // One wave of resident workgroups, or, where that takes chunks of more than 64
+  // planes, short chunks in many waves: a wave and a part of one leaves CUs idle
+  // at the end, and long chunks spread the accesses.  A cycle's time with chunks
+  // of 64, 16 and 40 planes: float32 448^3 1263, 1120, 1161 us, 512^3 1727, 1631
+  // and 1710; float64 400 x 480 x 360 1633, 1631 and 1575.
   const StripGrid g = strip_grid_rs(S, R, WY, L.nx, L.ny, L.nz,
-                                    std::max(1, resident_wgs(kern, 64 * WY, slots) / bt.nb));
+                                    std::max(1, resident_wgs(kern, 64 * WY, slots) / bt.nb), sizeof(T) == 4 ? 16 : 40);
   hipLaunchKernelGGL(kern, dim3(g.nblk, bt.nb), dim3(64 * WY), 0, st, L, u, b, out, bc, fc, g.zc, g.gx, g.gy, g.nblk,
                      part, bt, stop);
   return g.nblk;
