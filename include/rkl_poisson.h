@@ -319,7 +319,9 @@ typedef struct {
 rkl_status rkl_tune_set(const rkl_tune_entry *entries, int n);
 /* Drop every tile entry and every stage-count entry. */
 rkl_status rkl_tune_clear(void);
-/* The choice in effect for a level (variant 0 if no fused tau-step applies). */
+/* The choice recorded for a level: its entry, or the built-in base choice, whose
+ * strip shape and chunk length a launch on a level without an entry fits to the
+ * level's size and the device (variant 0 if no fused tau-step applies). */
 rkl_status rkl_tune_get(const rkl_grid *level, int s, int prec, rkl_tune_entry *out);
 /*
  * Time every variant and target on one level shape: reps launches each on

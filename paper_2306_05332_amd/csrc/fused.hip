@@ -649,10 +649,26 @@ static FusedChoice strip_filling(int variant, int s, int nx, int ny, int nz, int
   return FusedChoice{variant, chunks * per};
 }
 
-// Built-in choice for levels without a timed entry.  Lines drawn from timing
+// Built-in base choice, which rkl_tune_get reports for a level without a timed
+// entry: the strip kernel, 8-row strips for large float64 levels and 4-row
+// strips otherwise; stage counts the strip kernel is not built for take the
+// z-queue kernel on large levels and the LDS-ring kernel on small ones.
+template <typename T>
+FusedChoice fused_base(const LevelView<T>& L, int s) {
+  if (level_is_2d(L)) return FusedChoice{(sizeof(T) == 8 && s <= 2) ? FV_STRIP2D_8 : FV_STRIP2D_4, 2048};
+  if (fused_variant_ok<T>(FV_STRIP_4x4, s)) {
+    const bool big = (size_t)L.nx * L.ny * L.nz >= ((size_t)192 * 192 * 192);
+    if (sizeof(T) == 8 && L.periodic && big) return FusedChoice{FV_STRIP_8x4, 1024};
+    return FusedChoice{FV_STRIP_4x4, 1024};
+  }
+  if (fused_variant_ok<T>(FV_ZQ_64x32, s) && L.nx >= 128 && L.ny >= 128 && L.nz >= 64) return FusedChoice{FV_ZQ_64x32, 256};
+  return FusedChoice{FV_RING_64x4, 1024};
+}
+
+// What such a level runs: where the base choice is a strip, the strip shape and
+// chunk length that suit its size and the device.  Lines drawn from timing
 // every strip shape and chunk length on 25 shapes from 20 x 24 x 28 to 320 x
-// 384 x 384 (s = 2); means of the gain over four-row strips at 1024 workgroups
-// (large periodic float64 levels: eight-row ones), which stood here before:
+// 384 x 384 (s = 2); means of the gain over the base choice:
 //  * float64, periodic: stacked two-row strips, two workgroups per CU, from
 //    1.25 million cells (256^3 101 -> 82 us, 190 x 256 x 384 117 -> 96,
 //    160^3 25 -> 23), five-row one-wavefront strips, one per SIMD, below (100^3
@@ -664,12 +680,9 @@ static FusedChoice strip_filling(int variant, int s, int nx, int ny, int nz, int
 //    164 -> 125) or four-row strips (Dirichlet, 164 -> 152), else four-row strips
 //    at four workgroups per CU, small periodic levels five-row ones; 1.06 x
 //    periodic, 1.01 x Dirichlet.
-// Stage counts the strip kernel is not built for take the z-queue kernel on
-// large levels and the LDS-ring kernel on small ones.
 template <typename T>
 FusedChoice fused_heuristic(const LevelView<T>& L, int s) {
-  if (level_is_2d(L)) return FusedChoice{(sizeof(T) == 8 && s <= 2) ? FV_STRIP2D_8 : FV_STRIP2D_4, 2048};
-  if (fused_variant_ok<T>(FV_STRIP_4x4, s)) {
+  if (!level_is_2d(L) && fused_variant_ok<T>(FV_STRIP_4x4, s)) {
     const size_t n = (size_t)L.nx * L.ny * L.nz;
     const bool big = 3 * sizeof(T) * n > ((size_t)256 << 20);
     auto fill = [&](int variant, int slots) { return strip_filling(variant, s, L.nx, L.ny, L.nz, slots); };
@@ -680,8 +693,7 @@ FusedChoice fused_heuristic(const LevelView<T>& L, int s) {
     if (big) return L.periodic ? fill(FV_STRIPYX_8x4, 512) : fill(FV_STRIPYX_4x8, 512);
     return L.periodic && n < 1250000 ? fill(FV_STRIP_5x1, 1024) : fill(FV_STRIP_4x4, 1024);
   }
-  if (fused_variant_ok<T>(FV_ZQ_64x32, s) && L.nx >= 128 && L.ny >= 128 && L.nz >= 64) return FusedChoice{FV_ZQ_64x32, 256};
-  return FusedChoice{FV_RING_64x4, 1024};
+  return fused_base<T>(L, s);
 }
 
 // A batch's launch covers nb members at once, so the workgroups a level aims
@@ -697,15 +709,27 @@ static FusedChoice for_batch(FusedChoice c, int nb) {
   return c;
 }
 
+// the level's timed entry, if it has one that fits
+template <typename T>
+static bool fused_timed(const LevelView<T>& L, int s, FusedChoice& c) {
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  auto it = g_tune.find(TuneKey{L.nx, L.ny, L.nz, L.periodic ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s});
+  if (it == g_tune.end() || !fused_variant_ok<T>(it->second.variant, s) || !variant_fits(L, it->second.variant))
+    return false;
+  c = it->second;
+  return true;
+}
+
+template <typename T>
+FusedChoice fused_recorded(const LevelView<T>& L, int s) {
+  FusedChoice c;
+  return fused_timed<T>(L, s, c) ? c : fused_base<T>(L, s);
+}
+
 template <typename T>
 FusedChoice fused_choice(const LevelView<T>& L, int s, int nb) {
-  {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tune.find(TuneKey{L.nx, L.ny, L.nz, L.periodic ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s});
-    if (it != g_tune.end() && fused_variant_ok<T>(it->second.variant, s) && variant_fits(L, it->second.variant))
-      return for_batch(it->second, nb);
-  }
-  return for_batch(fused_heuristic<T>(L, s), nb);
+  FusedChoice c;
+  return for_batch(fused_timed<T>(L, s, c) ? c : fused_heuristic<T>(L, s), nb);
 }
 
 template <typename T, int S>
@@ -1055,6 +1079,7 @@ const char* fused_variant_name(int variant) {
   template bool fused_tau_supported<T>(const LevelView<T>&, int);                                                 \
   template bool fused_variant_ok<T>(int, int);                                                                    \
   template FusedChoice fused_choice<T>(const LevelView<T>&, int, int);                                            \
+  template FusedChoice fused_recorded<T>(const LevelView<T>&, int);                                               \
   template size_t fused_tau_blocks<T>(const LevelView<T>&, int, int);                                             \
   template size_t fused_tau_blocks_as<T>(const LevelView<T>&, FusedChoice, int);                                  \
   template int fused_chunk_blocks<T>(const LevelView<T>&, int, int);                                              \

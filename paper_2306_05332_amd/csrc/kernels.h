@@ -179,6 +179,9 @@ template <typename T>
 bool fused_variant_ok(int variant, int s);
 template <typename T>
 FusedChoice fused_choice(const LevelView<T>& L, int s, int nb = 1);  // nb: members of the batch
+// the timed entry, else the built-in base choice (what rkl_tune_get reports)
+template <typename T>
+FusedChoice fused_recorded(const LevelView<T>& L, int s);
 template <typename T>
 size_t fused_tau_blocks_as(const LevelView<T>& L, FusedChoice c, int s);
 // workgroups per z chunk of a strip variant on this level (0: not a strip

@@ -157,10 +157,10 @@ rkl_status rkl_tune_get(const rkl_grid* level, int s, int prec, rkl_tune_entry* 
     FusedChoice c{FV_HEUR, 0};
     if (prec == RKL_FP64) {
       const LevelView<double> V = view<double>(Lv, per, nullptr);
-      if (fused_tau_supported<double>(V, s)) c = fused_choice<double>(V, s);
+      if (fused_tau_supported<double>(V, s)) c = fused_recorded<double>(V, s);
     } else if (prec == RKL_MIXED) {
       const LevelView<float> V = view<float>(Lv, per, nullptr);
-      if (fused_tau_supported<float>(V, s)) c = fused_choice<float>(V, s);
+      if (fused_tau_supported<float>(V, s)) c = fused_recorded<float>(V, s);
     } else {
       fail(RKL_EINVAL, "unknown precision");
     }
