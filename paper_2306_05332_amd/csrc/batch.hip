@@ -127,14 +127,15 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   const LevelView<double> V0 = view<double>(F, P.periodic, nullptr);
   const LevelView<T> VT = view<T>(F, P.periodic, nullptr);
   launch_residual<double, T>(V0, C.phi, C.f0, H.b[0], C.part, stop, st, Batch{nb, (long long)F.n, 0, CONV_INTS, ps});
-  launch_check(C.part, (int)defect_blocks(F.nx, F.ny, F.nz, nb), 2, C.res0sq, o.tol, o.max_cycles, (double)F.n, C.conv,
-               st, Batch{nb, 0, 0, 0, ps});
+  const CheckArgs chk{C.part, (int)defect_blocks(F.nx, F.ny, F.nz, nb), 2, C.res0sq, o.tol, o.max_cycles, (double)F.n,
+                      C.conv, ps};
   check_launch();  // periodic: no level-0 mean pass (the defect is mean-free up to rounding; see solve_mixed)
   T* cur = H.u[0];
   T* alt = H.t[0];
   const Batch b0{nb, (long long)F.n, 0, CONV_INTS, ps};
   const VBatch vb{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw};
   const int down = level0_down<T>(P, H, nullptr, H.b[0], cur, o, nullptr, nullptr, stop, st, vb);
+  if (down == 0) launch_check(chk, st, nb);
   int pre_done = 0;
   if (down > 0) {
     pre_done = o.n_pre;
@@ -143,7 +144,7 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   } else {
     launch_fill<T>(cur, F.n, (T)0, stop, st, b0);
   }
-  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
+  vcycle_from<T>(P, H, cur, alt, H.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down, down > 0 ? &chk : nullptr);
   launch_add_cast<T>(C.phi, cur, F.n, stop, st, Batch{nb, (long long)F.n, (long long)F.n, CONV_INTS, 0});
   check_launch();
 }
@@ -172,10 +173,11 @@ void class_iteration_direct(ClassPlan& C, const rkl_opts& o, hipStream_t st, int
                      pair0 ? F.smooth2 : F.smooth, C.part, stop, st, gs, b0);
     nblk = (int)(gs ? gsrb_blocks<double>(V0, nb) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s, nb));
   }
-  launch_check(C.part, nblk, 1, C.res0sq, o.tol, o.max_cycles, 1.0, C.conv, st, Batch{nb, 0, 0, 0, ps});
+  const CheckArgs chk{C.part, nblk, 1, C.res0sq, o.tol, o.max_cycles, 1.0, C.conv, ps};
+  if (down == 0) launch_check(chk, st, nb);
   check_launch();
   vcycle_from<double>(P, H, cur, alt, C.f0, nullptr, down > 0 ? o.n_pre : (pair0 ? 2 : 1), o, stop, st, vb, true,
-                      nullptr, down);
+                      nullptr, down, down > 0 ? &chk : nullptr);
   for (int k = 0; k < 3; ++k)
     if (bufs[k] == cur) ia = k;
 }

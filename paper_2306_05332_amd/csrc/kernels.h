@@ -51,8 +51,19 @@ template <typename T>
 void launch_restrict(int fnx, int fny, int fnz, const T* fine, T* coarse, hipStream_t st);
 void launch_reduce(const double* part, int nblk, int stride, int nq, double* out, const int* stop,
                    hipStream_t st, const Batch& bt = single_batch());
-void launch_check(const double* part, int nblk, int stride, const double* res0sq, double tol, int max_cycles,
-                  double count, ConvState* cs, hipStream_t st, const Batch& bt = single_batch());
+// A cycle's convergence test (check.h) on nblk partial sums `stride` apart; a
+// batch's members at part + m part_stride, res0sq + m, cs + m.
+struct CheckArgs {
+  const double* part;
+  int nblk, stride;
+  const double* res0sq;
+  double tol;
+  int max_cycles;
+  double count;
+  ConvState* cs;
+  int part_stride;
+};
+void launch_check(const CheckArgs& A, hipStream_t st, int nb = 1);
 // member m (bt.nb members): out + m * s0 = c * (tab[m] - sum[m * s1] / count)
 // (sum nullptr: c * tab[m]); partials as launch_scale's at part + m * part_stride
 void launch_scale_tab(const double* const* tab, double* out, size_t n, double c, const double* sum, double count,
@@ -343,18 +354,20 @@ bool tail_fits(const TailShape& ts, int s, bool direct);
 // b_top: restricted right-hand side of the top tail level (mean not yet
 // removed); u_top receives that level's correction.  smooth[l]: the s stage
 // coefficients of tail level l.  dir: tables of the direct coarsest solve, or
-// nullptr for the accelerated RKL iteration (cs, ctol, cmax).
+// nullptr for the accelerated RKL iteration (cs, ctol, cmax).  chk: a convergence
+// test to run on the way (the tail itself runs even if it decides to stop).
 void tail_prepare();
 template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
-                 hipStream_t st, const Batch& bt = single_batch(), int gs = 0, const DirectTables* dir = nullptr);
+                 hipStream_t st, const Batch& bt = single_batch(), int gs = 0, const DirectTables* dir = nullptr,
+                 const CheckArgs* chk = nullptr);
 // The same tail in column form (tail_col.hip); false when the tail does not
 // have it (the caller takes launch_tail).
 void tail_col_prepare();
 template <typename T>
 bool launch_tail_col(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                      const T* b_top, T* u_top, const int* stop, hipStream_t st, const Batch& bt,
-                     const DirectTables& dir);
+                     const DirectTables& dir, const CheckArgs* chk);
 
 }  // namespace rkl

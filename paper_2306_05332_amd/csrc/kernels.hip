@@ -12,6 +12,7 @@
 // Kernels launched inside a V-cycle take `stop`: once the device-side
 // convergence test has set it, they return at once (the host may have queued
 // more cycles than were needed).
+#include "check.h"
 #include "kernels.h"
 
 #include <algorithm>
@@ -362,73 +363,17 @@ __global__ __launch_bounds__(RED_NT) void k_reduce(const double* __restrict__ pa
 }
 
 // ---------------------------------------------------------------- convergence test
-// One block: rel = sqrt(sum of part[b * stride]) / sqrt(res0sq) for the state at the
-// start of cycle cs->m; records it and decides, in this order:
-// non-finite -> RKL_ENONFINITE; rel <= tol -> done; three consecutive
-// increases that end above twice the best residual so far -> RKL_EDIVERGED;
-// with tol > 0, the last eight states all above 0.9 of the best state
-// before them (the residual has stopped falling, as it does at the float64
-// rounding floor of M u - f, about eps Lambda ||u|| / ||f||) -> RKL_ENOCONV,
-// marked stalled (tol = 0 asks for exactly max_cycles cycles);
-// m >= max_cycles -> RKL_ENOCONV.  Also stores the mean of the residual
-// (part[b * stride + 1] / count) as a diagnostic.
-__global__ __launch_bounds__(RED_NT) void k_check(const double* __restrict__ part, int nblk, int stride,
-                                                  const double* __restrict__ res0sq, double tol,
-                                                  int max_cycles, double count, ConvState* __restrict__ cs,
-                                                  Batch bt) {
-  __shared__ double sh[RED_NT / WAVE];
-  {
-    const long long mb = blockIdx.x;  // one workgroup per member
-    part += mb * bt.part_stride;
-    res0sq += mb;
-    cs += mb;
-  }
-  if (cs->stop) return;
-  double v2 = 0.0, v1 = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += RED_NT) {
-    v2 += part[(size_t)b * stride];
-    if (stride > 1) v1 += part[(size_t)b * stride + 1];
-  }
-  const double t2 = block_sum<RED_NT>(v2, sh);
-  const double t1 = block_sum<RED_NT>(v1, sh);
-  if (threadIdx.x != 0) return;
-  const int m = cs->m;
-  const double rel = sqrt(t2) / sqrt(res0sq[0]);
-  cs->mean = t1 / count;
-  if (m < CONV_HIST) cs->hist[m] = rel;
-  cs->last[m & 3] = rel;
-  // best residual up to the first of the last four states (three increases)
-  // and before the last eight states (stall window)
-  constexpr int SW = 8;
-  double best3 = HUGE_VAL, bestw = HUGE_VAL;
-  const int hmax = m < CONV_HIST ? m : CONV_HIST;
-  for (int q = 0; q < hmax; ++q) {
-    if (q <= m - 3) best3 = fmin(best3, cs->hist[q]);
-    if (q <= m - SW) bestw = fmin(bestw, cs->hist[q]);
-  }
-  double recent = rel;
-  for (int q = m - SW + 1; q < m; ++q)
-    if (q >= 0 && q < CONV_HIST) recent = fmin(recent, cs->hist[q]);
-  int status = 1;  // 1: keep going
-  int stalled = 0;
-  if (!isfinite(rel)) status = -5;
-  else if (rel <= tol) status = 0;
-  else if (m >= 3 && cs->last[m & 3] > cs->last[(m - 1) & 3] && cs->last[(m - 1) & 3] > cs->last[(m - 2) & 3] &&
-           cs->last[(m - 2) & 3] > cs->last[(m - 3) & 3] && rel > 2.0 * best3)
-    status = -4;
-  else if (tol > 0.0 && m >= SW && m < CONV_HIST && recent > 0.9 * bestw) {
-    status = -3;
-    stalled = 1;
-  } else if (m >= max_cycles) status = -3;
-  cs->rel = rel;
-  if (status != 1) {
-    cs->status = status;
-    cs->stalled = stalled;
-    cs->result_m = m;
-    cs->stop = 1;
-  } else {
-    cs->m = m + 1;
-  }
+__global__ __launch_bounds__(RED_NT) void k_check(CheckArgs A) {
+  __shared__ double sh[2 * RED_NT / WAVE];
+  const long long mb = blockIdx.x;  // one workgroup per member
+  A.part += mb * A.part_stride;
+  A.res0sq += mb;
+  A.cs += mb;
+  const int stop = A.cs->stop;
+  CheckLoads L;
+  check_load(A, RED_NT, L);
+  if (stop) return;
+  check_finish<RED_NT>(A, L, sh);
 }
 
 // ---------------------------------------------------------------- elementwise
@@ -673,10 +618,8 @@ void launch_reduce(const double* part, int nblk, int stride, int nq, double* out
   hipLaunchKernelGGL(k_reduce, dim3(bt.nb), dim3(RED_NT), 0, st, part, nblk, stride, nq, out, bt, stop);
 }
 
-void launch_check(const double* part, int nblk, int stride, const double* res0sq, double tol, int max_cycles,
-                  double count, ConvState* cs, hipStream_t st, const Batch& bt) {
-  hipLaunchKernelGGL(k_check, dim3(bt.nb), dim3(RED_NT), 0, st, part, nblk, stride, res0sq, tol, max_cycles,
-                     count, cs, bt);
+void launch_check(const CheckArgs& A, hipStream_t st, int nb) {
+  hipLaunchKernelGGL(k_check, dim3(nb), dim3(RED_NT), 0, st, A);
 }
 
 void launch_scale_tab(const double* const* tab, double* out, size_t n, double c, const double* sum, double count,

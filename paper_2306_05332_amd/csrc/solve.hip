@@ -262,34 +262,29 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
       double* a = bufs[ia];
       double *cur, *alt;
       int pre_done;
-      int nblk, stride;
       const VBatch vb{1, 0, 0, P.dscal};
       // small grids: the whole downstroke, with the residual norm of the start
       // state (not from the zero iterate, whose residual is f)
       const int down =
           cold0 && m == 0 ? 0 : level0_down<double>(P, P.h64, a, P.f0, bufs[ib], o, P.part, nullptr, stop, st, vb);
+      CheckArgs chk{P.part, down, 1, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, 0};
       if (down > 0) {
         cur = bufs[ib];
         alt = bufs[ic];
-        nblk = down;
-        stride = 1;
-        launch_check(P.part, nblk, stride, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, st);
-        check_launch();
         pre_done = o.n_pre;
       } else if (fused0) {
         // first relaxation, fused with the residual norm of the start state
         tau_keep<double>(P, V0, (cold0 && m == 0) ? nullptr : a, bufs[ib], bufs[ic], cur, alt, P.f0,
                          pair0 ? F.smooth2 : F.smooth, P.part, stop, st, gs);
-        nblk = (int)(gs ? gsrb_blocks<double>(V0) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s));
-        stride = 1;
-        launch_check(P.part, nblk, stride, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, st);
+        chk.nblk = (int)(gs ? gsrb_blocks<double>(V0) : fused_tau_blocks<double>(V0, pair0 ? 2 * o.s : o.s));
+        launch_check(chk, st);
         check_launch();
         pre_done = pair0 ? 2 : 1;
       } else {
         launch_residual<double, double>(V0, a, P.f0, (double*)nullptr, P.part, stop, st);
-        nblk = (int)defect_blocks(F.nx, F.ny, F.nz);
-        stride = 2;
-        launch_check(P.part, nblk, stride, Res0Sqrt::ptr(P), o.tol, o.max_cycles, 1.0, P.dconv, st);
+        chk.nblk = (int)defect_blocks(F.nx, F.ny, F.nz);
+        chk.stride = 2;
+        launch_check(chk, st);
         check_launch();
         if (o.n_pre > 0) {
           tau_keep<double>(P, V0, a, bufs[ib], bufs[ic], cur, alt, P.f0, F.smooth, nullptr, stop, st, gs);
@@ -304,7 +299,8 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
           pre_done = 0;
         }
       }
-      vcycle_from<double>(P, P.h64, cur, alt, P.f0, nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
+      vcycle_from<double>(P, P.h64, cur, alt, P.f0, nullptr, pre_done, o, stop, st, vb, true, nullptr, down,
+                          down > 0 ? &chk : nullptr);
       int ie = 0;
       for (int k = 0; k < 3; ++k)
         if (bufs[k] == cur) ie = k;
@@ -368,7 +364,7 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
       else  // zero_start: the first defect is f itself (phi = 0 is not read)
         launch_residual<double, float>(V0, (o.zero_start && queued == 0) ? nullptr : phi, P.f0, P.h32.b[0], P.part,
                                        stop, st);
-      launch_check(P.part, nblk, 2, Res0Sqrt::ptr(P), o.tol, o.max_cycles, (double)F.n, P.dconv, st);
+      const CheckArgs chk{P.part, nblk, 2, Res0Sqrt::ptr(P), o.tol, o.max_cycles, (double)F.n, P.dconv, 0};
       check_launch();
       // periodic: the defect of the mean-free f sums to zero up to rounding
       // (the periodic M sums to zero); the rounding-level mean that the
@@ -379,6 +375,7 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
       const VBatch vb{1, 0, 0, P.dscal};
       const int down =
           level0_down<float>(P, P.h32, nullptr, P.h32.b[0], cur, o, nullptr, nullptr, stop, st, vb);  // small grids
+      if (down == 0) launch_check(chk, st);
       int pre_done = 0;
       if (down > 0) {
         pre_done = o.n_pre;
@@ -388,7 +385,8 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
       } else {
         launch_fill<float>(cur, F.n, 0.0f, stop, st);
       }
-      vcycle_from<float>(P, P.h32, cur, alt, P.h32.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down);
+      vcycle_from<float>(P, P.h32, cur, alt, P.h32.b[0], nullptr, pre_done, o, stop, st, vb, true, nullptr, down,
+                         down > 0 ? &chk : nullptr);
       if (fold) eprev = cur;  // read by the next iteration's defect pass, before its V-cycle runs
       else launch_add_cast<float>(phi, cur, F.n, stop, st);
       check_launch();

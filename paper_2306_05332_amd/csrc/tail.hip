@@ -748,14 +748,15 @@ void tail_prepare() {
 template <typename T>
 void launch_tail(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                  CoarseSchedule cs, double ctol, int cmax, const T* b_top, T* u_top, const int* stop,
-                 hipStream_t st, const Batch& bt, int gs, const DirectTables* dir) {
+                 hipStream_t st, const Batch& bt, int gs, const DirectTables* dir, const CheckArgs* chk) {
   // The column form takes RKL smoothing of up to four stages with the direct
   // coarsest solve, on levels whose columns fit its threads: half the time of
   // this kernel or less (figures in tail_col.hip).  Gauss-Seidel, more stages,
   // a coarsest iteration and elongated levels stay here.
   if (dir != nullptr && !gs &&
-      launch_tail_col<T>(ts, smooth, s, n_pre, n_post, periodic, b_top, u_top, stop, st, bt, *dir))
+      launch_tail_col<T>(ts, smooth, s, n_pre, n_post, periodic, b_top, u_top, stop, st, bt, *dir, chk))
     return;
+  if (chk != nullptr) launch_check(*chk, st, bt.nb);
   TailArgs<T> A;
   std::memset(&A, 0, sizeof(A));
   A.gs = gs;
@@ -799,9 +800,11 @@ template bool tail_fits<double>(const TailShape&, int, bool);
 template bool tail_fits<float>(const TailShape&, int, bool);
 template void launch_tail<double>(const TailShape&, const StageCoef* const*, int, int, int, int, CoarseSchedule,
                                   double, int, const double*, double*, const int*, hipStream_t, const Batch&, int,
-                                  const DirectTables*);
+                                  const DirectTables*,
+                                  const CheckArgs*);
 template void launch_tail<float>(const TailShape&, const StageCoef* const*, int, int, int, int, CoarseSchedule,
                                  double, int, const float*, float*, const int*, hipStream_t, const Batch&, int,
-                                 const DirectTables*);
+                                 const DirectTables*,
+                                  const CheckArgs*);
 
 }  // namespace rkl

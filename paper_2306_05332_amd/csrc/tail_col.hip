@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "check.h"
 #include "direct.h"
 
 namespace rkl {
@@ -336,7 +337,7 @@ __device__ __forceinline__ void col_up(const ColLevel<T>& V, const ColLevel<T>& 
 
 template <typename T, bool PER, bool FLAT>
 __global__ __launch_bounds__(TCNT) void k_tail_col(ColArgs<T> A, const T* __restrict__ b_top, T* __restrict__ u_top,
-                                                   Batch bt, const int* __restrict__ stop) {
+                                                   Batch bt, const int* __restrict__ stop, CheckArgs chk) {
   extern __shared__ __align__(16) unsigned char pool_raw[];
   __shared__ double red[TCNT / WAVE];
   __shared__ double stab[TCTAB];
@@ -347,6 +348,9 @@ __global__ __launch_bounds__(TCNT) void k_tail_col(ColArgs<T> A, const T* __rest
     b_top += mb * bt.s0;
     u_top += mb * bt.s0;
     if (stop != nullptr) stop += mb * bt.stop_stride;
+    chk.part += mb * chk.part_stride;
+    chk.res0sq += mb;
+    chk.cs += mb;
     int cells = 0;  // the pool holds three arrays per level
     for (int l = 0; l < A.nlev; ++l) cells += 3 * A.lv[l].n;
     lds_poison(reinterpret_cast<T*>(pool_raw), cells);
@@ -365,6 +369,8 @@ __global__ __launch_bounds__(TCNT) void k_tail_col(ColArgs<T> A, const T* __rest
   Col C = col_of<T>(A.lv[0]);
   T b[TCM];
   const int stopped = stop != nullptr ? *stop : 0;
+  CheckLoads ck;
+  if (chk.nblk > 0) check_load(chk, TCNT, ck);
 #pragma unroll
   for (int m = 0; m < TCM; ++m) b[m] = m < C.cnt ? b_top[C.a + m * A.lv[0].nxy] : (T)0;
   double g[4];  // dense inverse: row tid / 16, columns 4 (tid % 16) ..
@@ -498,6 +504,7 @@ __global__ __launch_bounds__(TCNT) void k_tail_col(ColArgs<T> A, const T* __rest
     else col_up<T, PER, FLAT, 4, false>(V, N, C, sco[l], E, base, moved, A.s, A.n_post, top, now);
     swapped = (swapped & ~(1u << l)) | ((now ? 1u : 0u) << l);
   }
+  if (chk.nblk > 0) check_finish<TCNT>(chk, ck, stab);  // (stab: last read before the upstroke)
 }
 
 // cells per thread of a level: the fewest whose segments fit the workgroup and
@@ -542,7 +549,7 @@ void tail_col_prepare() {
 template <typename T>
 bool launch_tail_col(const TailShape& ts, const StageCoef* const* smooth, int s, int n_pre, int n_post, int periodic,
                      const T* b_top, T* u_top, const int* stop, hipStream_t st, const Batch& bt,
-                     const DirectTables& dir) {
+                     const DirectTables& dir, const CheckArgs* chk) {
   if (ts.nlev < 2 || s > TCS || n_pre < 1) return false;
   ColArgs<T> A;
   std::memset(&A, 0, sizeof(A));
@@ -581,13 +588,16 @@ bool launch_tail_col(const TailShape& ts, const StageCoef* const* smooth, int s,
   tail_col_prepare();
   auto k = periodic ? (flat ? k_tail_col<T, true, true> : k_tail_col<T, true, false>)
                     : (flat ? k_tail_col<T, false, true> : k_tail_col<T, false, false>);
-  hipLaunchKernelGGL(k, dim3(bt.nb), dim3(TCNT), shm, st, A, b_top, u_top, bt, stop);
+  hipLaunchKernelGGL(k, dim3(bt.nb), dim3(TCNT), shm, st, A, b_top, u_top, bt, stop,
+                     chk != nullptr ? *chk : CheckArgs{});
   return true;
 }
 
 template bool launch_tail_col<double>(const TailShape&, const StageCoef* const*, int, int, int, int, const double*,
-                                      double*, const int*, hipStream_t, const Batch&, const DirectTables&);
+                                      double*, const int*, hipStream_t, const Batch&, const DirectTables&,
+                                      const CheckArgs*);
 template bool launch_tail_col<float>(const TailShape&, const StageCoef* const*, int, int, int, int, const float*,
-                                     float*, const int*, hipStream_t, const Batch&, const DirectTables&);
+                                     float*, const int*, hipStream_t, const Batch&, const DirectTables&,
+                                     const CheckArgs*);
 
 }  // namespace rkl
