@@ -37,11 +37,24 @@ __device__ __forceinline__ void axis_apply(const double* in, double* out, const 
     const int base = lok ? (q / s) * (n * s) + q % s : 0;
     const int i = m0 + r;
     dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < n; k0 += 4) {
-      const int k = k0 + kq;
-      const double a = (i < n && k < n) ? (INV ? Q[k * n + i] : Q[i * n + k]) : 0.0;
-      const double b = (lok && k < n) ? in[base + k * s] : 0.0;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    // four steps' operands are loaded before the first is used (a step at a time,
+    // the latencies of the matrix loads added up: planes of 50 x 30 took 13.4 and
+    // 11.7 us forth and back in four wavefronts, 6.9 and 6.3 now in eight);
+    // out-of-range entries read the last one in range and count as 0
+    const int ic = min(i, n - 1);
+    for (int k0 = 0; k0 < n; k0 += 16) {
+      double a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = min(k0 + 4 * u + kq, n - 1);
+        a[u] = INV ? Q[k * n + ic] : Q[ic * n + k];
+        b[u] = in[base + k * s];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool kok = k0 + 4 * u + kq < n;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(i < n && kok ? a[u] : 0.0, lok && kok ? b[u] : 0.0, acc, 0, 0, 0);
+      }
     }
     if (lok) {
 #pragma unroll

@@ -16,7 +16,7 @@
 
 namespace rkl {
 
-constexpr int DNT = 256;                               // threads per workgroup
+constexpr int DNT = 512;                               // threads per workgroup
 constexpr size_t DIRECT_PLANE_LDS = 128 * 1024;        // LDS for a plane and its x transform
 constexpr int DIRECT_MAX_AXIS = 512;                   // 2 x 16 lines of one axis in LDS: 128 KB
 
