@@ -251,10 +251,12 @@ rkl_status rkl_coarse_solve_f32(const rkl_grid *grid, const rkl_opts *opts, cons
  * (float64 defect, V-cycle on the correction at the working precision,
  * float64 update) is captured once into a HIP graph and replayed until every
  * member has stopped.  A class whose hierarchy ends neither in the
- * one-workgroup coarse tail nor in a direct coarsest solve is solved member by
- * member with the single-solve path.  Returns the first non-OK member status in class order (each member's
- * own outcome is in stats[i]); phi of periodic members is mean-free.  Calls
- * on one process are serialised.  Buffers persist until rkl_release_all.
+ * one-workgroup coarse tail nor in a direct coarsest solve, or whose arrays do
+ * not fit the device's free memory, is solved member by member with the
+ * single-solve path.  Returns the first non-OK member status in class order
+ * (each member's own outcome is in stats[i]); phi of periodic members is
+ * mean-free.  Calls on one process are serialised.  Buffers persist until
+ * rkl_release_all.
  */
 rkl_status rkl_poisson_solve_batched(const rkl_grid *grids, int nbatch, const rkl_opts *opts,
                                      const double *const *rho, double *const *phi,

@@ -410,7 +410,17 @@ rkl_status solve_batched(const rkl_grid* grids, int nbatch, const rkl_opts& o, c
       single.insert(single.end(), kv.second.begin(), kv.second.end());
       continue;
     }
-    cls.push_back(&get_class(g, og, (int)kv.second.size()));
+    ClassPlan* C = nullptr;
+    try {
+      C = &get_class(g, og, (int)kv.second.size());
+    } catch (const Fail& e) {
+      if (e.st != RKL_ENOMEM) throw;
+    }
+    if (C == nullptr) {  // no room for the class's arrays: one member's are enough
+      single.insert(single.end(), kv.second.begin(), kv.second.end());
+      continue;
+    }
+    cls.push_back(C);
     members.push_back(kv.second);
   }
   rkl_status worst = RKL_OK;
