@@ -29,6 +29,7 @@ struct ClassPlan {
   Plan* base = nullptr;  // level descriptors, schedule tables and tail choice of one member
   int nb = 0;
   int s = 2;             // stages per tau-step of this class
+  size_t wide = 0;       // level-0 cells of all members of a wide class (wide_cells), else 0
   int part_stride = 0;
   double *f0 = nullptr, *phi = nullptr, *res0sq = nullptr, *dsum = nullptr, *part = nullptr;
   double* dirw = nullptr;  // scratch of the multi-workgroup direct coarsest solve
@@ -63,7 +64,22 @@ struct ClassPlan {
 
 std::map<ClassKey, std::unique_ptr<ClassPlan>> g_classes;
 
-ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
+// Wide classes: hierarchies without the tail of the accelerated iteration
+// (coarsest levels of more than 256 cells), which only the direct coarsest solve
+// lets run batched.  A member's single solve needs one member's arrays, a wide
+// class those of all (about 43 bytes a cell), so the classes of a call, and
+// likewise those kept between calls, hold at most WIDE_MAX_CELLS level-0 cells
+// together (a few GB); members beyond are solved one by one.
+constexpr size_t WIDE_MAX_CELLS = (size_t)1 << 26;
+template <typename T>
+size_t wide_cells(const Plan& P, size_t nb) {
+  return tail_level<T>(P, false) <= 0 ? nb * P.lv[0].n : 0;
+}
+
+void drop_idle_wide_classes(size_t cells, const std::vector<ClassPlan*>& keep);
+
+// keep: classes that the running call uses already
+ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb, const std::vector<ClassPlan*>& keep) {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   const int direct = (o.prec == RKL_FP64 && o.n_pre > 0) ? 1 : 0;
@@ -73,9 +89,12 @@ ClassPlan& get_class(const rkl_grid& g, const rkl_opts& o, int nb) {
   auto it = g_classes.find(key);
   if (it != g_classes.end()) return *it->second;
   if (nb > 65535) fail(RKL_EINVAL, "at most 65535 members per grid class");
+  const size_t wide = o.prec == RKL_MIXED ? wide_cells<float>(base, nb) : wide_cells<double>(base, nb);
+  if (wide > 0) drop_idle_wide_classes(wide, keep);
   auto C = std::make_unique<ClassPlan>();
   C->base = &base;
   C->nb = nb;
+  C->wide = wide;
   const Lev& F = base.lv[0];
   const int L = base.L();
   size_t ps = 2 * std::max(resid_blocks(F.nx, F.ny, F.nz), defect_blocks(F.nx, F.ny, F.nz));
@@ -327,6 +346,25 @@ struct GraphCache {
 };
 std::unique_ptr<GraphCache> g_graph;
 
+// Give back the wide classes of earlier calls if, with a new one of `cells`
+// cells, more than WIDE_MAX_CELLS would be held.  (Calls are serialised and end
+// synchronised, so none of them is running; the graph cached from the last call
+// may name their arrays and goes with them.)
+void drop_idle_wide_classes(size_t cells, const std::vector<ClassPlan*>& keep) {
+  size_t held = cells;
+  for (auto& c : g_classes) held += c.second->wide;
+  if (held <= WIDE_MAX_CELLS) return;
+  for (auto it = g_classes.begin(); it != g_classes.end();) {
+    ClassPlan* c = it->second.get();
+    if (c->wide == 0 || std::find(keep.begin(), keep.end(), c) != keep.end()) {
+      ++it;
+      continue;
+    }
+    g_graph.reset();
+    it = g_classes.erase(it);
+  }
+}
+
 // Capture `iters` outer iterations of every class into one graph (cached).
 // Classes share no buffer, so each is a branch of its own (forked from and
 // joined back into the capture stream by events): the latency-bound small
@@ -371,18 +409,14 @@ hipGraphExec_t batch_graph(std::vector<ClassPlan*>& cls, const rkl_opts& o, int 
 }
 
 // A class runs batched when its hierarchy ends in the one-workgroup tail or
-// in the direct coarsest solve and every level above takes the fused tau-step.
-// Hierarchies without the tail of the accelerated iteration (coarsest levels
-// of more than 256 cells) run batched only up to CLASS_MAX_CELLS level-0 cells
-// in the class, whose arrays are then at most a few GB; larger ones are solved
-// member by member, within one member's arrays.
-constexpr size_t CLASS_MAX_CELLS = (size_t)1 << 26;
+// in the direct coarsest solve and every level above takes the fused tau-step;
+// a wide class only up to `room` level-0 cells.
 template <typename T>
-bool class_ok(Plan& P, const rkl_opts& o, size_t nb) {
+bool class_ok(Plan& P, const rkl_opts& o, size_t nb, size_t room) {
   const bool direct = direct_coarse<T>(P, o);
   const int lt = tail_level<T>(P, direct);
   if (P.L() < 2 || (lt <= 0 && !direct)) return false;
-  if (tail_level<T>(P, false) <= 0 && nb * P.lv[0].n > CLASS_MAX_CELLS) return false;
+  if (wide_cells<T>(P, nb) > room) return false;
   const int sf = o.smoother == RKL_SMOOTH_GSRB ? 2 : o.s;
   for (int l = 0; l < (lt > 0 ? lt : P.L() - 1); ++l)
     if (!fused_tau_supported<T>(view<T>(P.lv[l], P.periodic, nullptr), sf)) return false;
@@ -400,19 +434,20 @@ rkl_status solve_batched(const rkl_grid* grids, int nbatch, const rkl_opts& o, c
   std::vector<ClassPlan*> cls;
   std::vector<std::vector<int>> members;
   std::vector<int> single;  // members solved one by one
+  size_t room = WIDE_MAX_CELLS;
   for (auto& kv : groups) {
     const rkl_grid& g = grids[kv.second[0]];
     const rkl_opts og = with_s(o, g);
     Plan& P = get_plan(g, og.s, og.tau_frac, og.min_coarse, og.prec);
-    const bool ok = og.prec == RKL_MIXED ? class_ok<float>(P, og, kv.second.size())
-                                         : class_ok<double>(P, og, kv.second.size());
+    const bool ok = og.prec == RKL_MIXED ? class_ok<float>(P, og, kv.second.size(), room)
+                                         : class_ok<double>(P, og, kv.second.size(), room);
     if (!ok) {
       single.insert(single.end(), kv.second.begin(), kv.second.end());
       continue;
     }
     ClassPlan* C = nullptr;
     try {
-      C = &get_class(g, og, (int)kv.second.size());
+      C = &get_class(g, og, (int)kv.second.size(), cls);
     } catch (const Fail& e) {
       if (e.st != RKL_ENOMEM) throw;
     }
@@ -420,6 +455,7 @@ rkl_status solve_batched(const rkl_grid* grids, int nbatch, const rkl_opts& o, c
       single.insert(single.end(), kv.second.begin(), kv.second.end());
       continue;
     }
+    room -= C->wide;
     cls.push_back(C);
     members.push_back(kv.second);
   }

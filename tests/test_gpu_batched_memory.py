@@ -42,3 +42,31 @@ def test_batch_without_room_for_its_class_is_solved_member_by_member():
     for k, (phi, st) in zip((0, nb - 1), ref):
         assert torch.equal(phis[k], phi) and stats[k].cycles == st.cycles
         np.testing.assert_array_equal(stats[k].history, st.history)
+
+
+def test_classes_kept_between_calls_are_bounded():
+    """Three batches of about 64 million cells (boxes of 40^3, coarsest level 10^3)
+    that differ in their member count, each a class of its own: 43 bytes a cell, so
+    one class is 2.6 GiB, and what the library holds stays below two of them."""
+    import paper_2306_05332_amd as R
+    n, h = 40, (1.0 / 40,) * 3
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rho = torch.randn((n, n, n), generator=g, dtype=torch.float64, device="cuda")
+    o = R.Options(tol=1e-3)
+    ref, st = R.solve(rho, h, "dirichlet", opts=o)
+    R.release_all()
+    R.solve_batched([rho] * 3, [h] * 3, "dirichlet", opts=o)
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    for nb in (1000, 1001, 1002):
+        phis, stats = R.solve_batched([rho] * nb, [h] * nb, "dirichlet", opts=o)
+        for k in (0, nb - 1):
+            assert stats[k].cycles == st.cycles
+            assert float((phis[k] - ref).abs().max()) <= 1e-13 * float(ref.abs().max())
+        del phis
+        torch.cuda.empty_cache()
+        held = free - torch.cuda.mem_get_info()[0]
+        print(f"{nb} members: {held / GIB:.2f} GiB held", flush=True)
+        assert held < 2 * 43 * 1000 * n ** 3
+    R.release_all()
