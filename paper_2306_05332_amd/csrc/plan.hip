@@ -2,6 +2,7 @@
 // stage coefficients, App. A.3 / A.4 stage counts), option checks, error
 // state, and the C-ABI entry points that configure rather than compute.
 
+#include "accel_steps.h"
 #include "solver_core.h"
 
 namespace rkl {
@@ -203,50 +204,6 @@ TailShape tail_shape(const Plan& P, int lt) {
   return ts;
 }
 
-// Tau-steps (at most 200, else 0) after which the accelerated schedule has
-// reduced every residual on level C to `tol` of its right-hand side: the
-// largest product of the steps' stage polynomials over the spectrum, sampled
-// at 2048 evenly and 512 logarithmically spaced |lambda| and at its ends.
-static int accel_steps_to(const Lev& C, bool periodic, double theta, const std::vector<int>& sched, double tol) {
-  const int ns[3] = {C.nx, C.ny, C.nz};
-  const double hs[3] = {C.hx, C.hy, C.hz};
-  double lo = periodic ? HUGE_VAL : 0.0, hi = 0.0;
-  for (int d = 0; d < 3; ++d) {
-    if (ns[d] == 1 && (periodic || std::isinf(hs[d]))) continue;
-    const double w = 4.0 / (hs[d] * hs[d]);
-    if (periodic) {
-      lo = std::min(lo, w * std::pow(std::sin(M_PI / ns[d]), 2));
-      hi += w * std::pow(std::sin(M_PI * (ns[d] / 2) / ns[d]), 2);
-    } else {
-      lo += w * std::pow(std::sin(M_PI / (2.0 * ns[d])), 2);
-      hi += w;
-    }
-  }
-  if (!(lo > 0.0) || !(hi >= lo) || !std::isfinite(hi)) return 0;
-  std::vector<double> x, amp;
-  for (int q = 0; q <= 2048; ++q) x.push_back(lo + (hi - lo) * q / 2048.0);
-  for (int q = 1; q < 512; ++q) x.push_back(lo * std::pow(hi / lo, q / 512.0));
-  for (double& v : x) v = 1.0 - theta * C.dtpar * v;
-  amp.assign(x.size(), 1.0);
-  for (int step = 0; step < 200; ++step) {
-    const int s = sched[std::min<size_t>(step, sched.size() - 1)];
-    double worst = 0.0;
-    for (size_t q = 0; q < x.size(); ++q) {
-      double p0 = 1.0, p1 = x[q];  // P_s by the three-term recursion
-      for (int j = 2; j <= s; ++j) {
-        const double pn = ((2.0 * j - 1.0) / j) * x[q] * p1 - ((j - 1.0) / j) * p0;
-        p0 = p1;
-        p1 = pn;
-      }
-      amp[q] *= p1;
-      worst = std::max(worst, std::fabs(amp[q]));
-    }
-    if (worst <= tol) return step + 1;
-    if (!(worst < 1e6)) return 0;
-  }
-  return 0;
-}
-
 // Orthonormal eigenvectors (rows) and eigenvalues of one axis of the coarsest
 // operator: with the ghost -u, sqrt(2/n) sin(pi (k+1)(i+1/2)/n) (the last one
 // over sqrt 2) at -4 sin^2(pi (k+1)/2n) / h^2; periodic, the constant, pairs
@@ -379,10 +336,11 @@ Plan& get_plan(const rkl_grid& g, int s, double theta, int min_coarse, int prec)
     }
   }
   if (L >= 2 && direct_axes_ok(C.nx, C.ny, C.nz)) {
-    P->steps64 = accel_steps_to(C, P->periodic, theta, P->sched, 1e-13);
-    P->steps32 = accel_steps_to(C, P->periodic, theta, P->sched, 1e-6);
     const int n[3] = {C.nx, C.ny, C.nz};
     const double h[3] = {C.hx, C.hy, C.hz};
+    const AccelSteps steps = accel_steps(n, h, C.dtpar, P->periodic, theta, P->sched, 1e-6, 1e-13);
+    P->steps64 = steps.tight;
+    P->steps32 = steps.loose;
     size_t nq = 0, nl = 0;
     for (int d = 0; d < 3; ++d) {
       nq += (size_t)n[d] * n[d];

@@ -94,8 +94,8 @@ struct Plan {
   int tail64 = -1, tail32 = -1;  // first level run by the one-workgroup tail (-1: none)
   // direct coarsest solve (tab nullptr: not available on this hierarchy), the
   // tail's first level with it, the scratch of its multi-workgroup form and
-  // the tau-steps in which the accelerated iteration surely reaches the default
-  // tolerance of either precision (0: not within 200)
+  // the tau-steps in which the accelerated iteration reaches the default
+  // tolerance of either precision (accel_steps.h; 0: not within 200)
   DirectTables direct{0, 0, 0, nullptr, nullptr};
   int dtail64 = -1, dtail32 = -1;
   double* dirw = nullptr;
