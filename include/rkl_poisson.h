@@ -297,13 +297,16 @@ int rkl_tau_step_launches(const rkl_grid *grid, int s, int prec);
  *          13  as 11 with 8 wavefronts of 8 rows
  *          14  as 11 with 8 wavefronts of 2 rows (s <= 2)
  *          15  as 11 with 16 wavefronts of 2 rows (s <= 2)
- *          13  as 11 with 8 wavefronts of 8 rows
  *              (strip: s <= 2 in float64, s <= 3 in float32; variants 8 and 9
  *              are for two-dimensional levels, nz = 1 with hz = inf, and
  *              those levels take no other variant)
  * Entries are keyed by (nx, ny, nz, bc, prec, s) of one multigrid LEVEL
  * (prec RKL_FP64: float64 sweeps; RKL_MIXED: the float32 sweeps of the
  * mixed path) and take effect at the next solve.  The table is per process.
+ * An entry with a time chooses the strip shape of a level; small and
+ * two-dimensional levels still take one launch per V-cycle stroke, whatever it
+ * names.  An entry with us = 0 holds the level's strokes to that shape as well:
+ * they run as the tau-steps and fused transfers of its strips.
  */
 typedef struct {
     int nx, ny, nz;      /* level shape                                      */
@@ -312,7 +315,8 @@ typedef struct {
     int s;               /* stages per tau-step                              */
     int variant;         /* see above                                        */
     int target;          /* workgroups aimed for (>= 1)                      */
-    double us;           /* rkl_autotune: mean launch time in microseconds   */
+    double us;           /* mean launch time in microseconds (rkl_autotune), */
+                         /* or 0 in an entry set by hand                     */
 } rkl_tune_entry;
 
 /* Install n entries (host array).  RKL_EINVAL for a malformed entry, a

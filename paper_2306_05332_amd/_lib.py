@@ -565,7 +565,10 @@ def _entry_c(d):
 
 
 def tune_set(entries):
-    """Install tile choices (dicts as returned by autotune_level / tune_get)."""
+    """Install tile choices (dicts as returned by autotune_level / tune_get).
+    One without a time ("us" absent or 0) also holds the level's V-cycle strokes
+    to its strips, where small and two-dimensional levels otherwise take one
+    launch per stroke."""
     lib = load_library()
     arr = (c_tune * max(1, len(entries)))(*[_entry_c(d) for d in entries])
     _check(lib.rkl_tune_set(arr, len(entries)))

@@ -424,6 +424,7 @@ static int brick_len(BrickArgs<T>& A, const LevelView<T>& L, int s, const StageC
 template <typename T>
 int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* bc, int s, const StageCoef* co,
                       int steps, double* rsum, double* csum, const int* stop, hipStream_t st, const Batch& bt) {
+  if (fused_pinned<T>(L, s)) return 0;
   if (level_is_2d(L)) return launch_win2_down<T>(L, u0, b, u, bc, s, co, steps, rsum, csum, stop, st, bt);
   BrickArgs<T> A;
   const bool zero = u0 == nullptr;
@@ -445,6 +446,7 @@ int launch_brick_down(const LevelView<T>& L, const T* u0, const T* b, T* u, T* b
 template <typename T>
 bool launch_brick_up(const LevelView<T>& L, const T* u, const T* e, const T* b, T* out, int s, const StageCoef* co,
                      int steps, const int* stop, hipStream_t st, const Batch& bt) {
+  if (fused_pinned<T>(L, s)) return false;
   if (level_is_2d(L)) return launch_win2_up<T>(L, u, e, b, out, s, co, steps, stop, st, bt) > 0;
   BrickArgs<T> A;
   const int len = brick_len(A, L, s, co, steps, (s * steps + 1) & ~1, bt.nb, BRICK_SLOTS);

@@ -709,9 +709,9 @@ static FusedChoice for_batch(FusedChoice c, int nb) {
   return c;
 }
 
-// the level's timed entry, if it has one that fits
+// the level's entry, if it has one that fits
 template <typename T>
-static bool fused_timed(const LevelView<T>& L, int s, FusedChoice& c) {
+static bool fused_entry(const LevelView<T>& L, int s, FusedChoice& c) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tune.find(TuneKey{L.nx, L.ny, L.nz, L.periodic ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s});
   if (it == g_tune.end() || !fused_variant_ok<T>(it->second.variant, s) || !variant_fits(L, it->second.variant))
@@ -723,13 +723,20 @@ static bool fused_timed(const LevelView<T>& L, int s, FusedChoice& c) {
 template <typename T>
 FusedChoice fused_recorded(const LevelView<T>& L, int s) {
   FusedChoice c;
-  return fused_timed<T>(L, s, c) ? c : fused_base<T>(L, s);
+  return fused_entry<T>(L, s, c) ? c : fused_base<T>(L, s);
+}
+
+template <typename T>
+bool fused_pinned(const LevelView<T>& L, int s) {
+  FusedChoice c;
+  if (fused_entry<T>(L, s, c) && c.pinned) return true;
+  return level_is_2d(L) && fused_entry<T>(L, 2 * s, c) && c.pinned;
 }
 
 template <typename T>
 FusedChoice fused_choice(const LevelView<T>& L, int s, int nb) {
   FusedChoice c;
-  return for_batch(fused_timed<T>(L, s, c) ? c : fused_heuristic<T>(L, s), nb);
+  return for_batch(fused_entry<T>(L, s, c) ? c : fused_heuristic<T>(L, s), nb);
 }
 
 template <typename T, int S>
@@ -1080,6 +1087,7 @@ const char* fused_variant_name(int variant) {
   template bool fused_variant_ok<T>(int, int);                                                                    \
   template FusedChoice fused_choice<T>(const LevelView<T>&, int, int);                                            \
   template FusedChoice fused_recorded<T>(const LevelView<T>&, int);                                               \
+  template bool fused_pinned<T>(const LevelView<T>&, int);                                                        \
   template size_t fused_tau_blocks<T>(const LevelView<T>&, int, int);                                             \
   template size_t fused_tau_blocks_as<T>(const LevelView<T>&, FusedChoice, int);                                  \
   template int fused_chunk_blocks<T>(const LevelView<T>&, int, int);                                              \

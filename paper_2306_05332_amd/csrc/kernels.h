@@ -185,6 +185,7 @@ inline bool level_is_2d(const LevelView<T>& L) { return L.nz == 1 && L.ihz2 == (
 struct FusedChoice {
   int variant;
   int target;
+  bool pinned = false;  // an entry set by hand (no time): the level's strokes stay with the strips
 };
 template <typename T>
 bool fused_variant_ok(int variant, int s);
@@ -193,6 +194,10 @@ FusedChoice fused_choice(const LevelView<T>& L, int s, int nb = 1);  // nb: memb
 // the timed entry, else the built-in base choice (what rkl_tune_get reports)
 template <typename T>
 FusedChoice fused_recorded(const LevelView<T>& L, int s);
+// whether the level has a pinned entry for s stages (two-dimensional levels: or
+// for a pair of such tau-steps)
+template <typename T>
+bool fused_pinned(const LevelView<T>& L, int s);
 template <typename T>
 size_t fused_tau_blocks_as(const LevelView<T>& L, FusedChoice c, int s);
 // workgroups per z chunk of a strip variant on this level (0: not a strip
@@ -313,7 +318,8 @@ void launch_direct(const DirectTables& D, const T* b, T* u, double* W, const int
                    const Batch& bt = single_batch());
 
 // Strokes of small 3-D levels in one launch (brick.hip; RKL, even extents, no
-// face data, s steps <= 4): false or 0 when the level does not take them.
+// face data, s steps <= 4): false or 0 when the level does not take them, or is
+// pinned to a strip shape (fused_pinned), whose fused passes then run.
 // down: u = u0 (nullptr: the zero iterate) after `steps` tau-steps, bc =
 // R(b - M u); u distinct from u0.  Returns the workgroup count, each of which
 // writes its sum of (M u0 - b)^2 to rsum[blk] (u0 given) and of its coarse

@@ -132,7 +132,7 @@ rkl_status rkl_tune_set(const rkl_tune_entry* entries, int n) {
     }
     for (int q = 0; q < n; ++q) {
       const rkl_tune_entry& e = entries[q];
-      tune_install(e.nx, e.ny, e.nz, e.bc == RKL_BC_PERIODIC, e.prec == RKL_FP64, e.s, FusedChoice{e.variant, e.target});
+      tune_install(e.nx, e.ny, e.nz, e.bc == RKL_BC_PERIODIC, e.prec == RKL_FP64, e.s, FusedChoice{e.variant, e.target, e.us == 0.0});
     }
     return RKL_OK;
   });
