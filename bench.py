@@ -108,7 +108,7 @@ def kernel_symbol(R, shape, s, prec="fp64"):
     effect (strip kernels: up to the last template argument, the store-hint
     flag, which the launcher picks from the level's size)."""
     tname = "double" if prec == "fp64" else "float"
-    v = R.tune_get(shape, s, "periodic", prec)["variant"]
+    v = R.tune_launched(shape, s, "periodic", prec)["variant"]
     strip = {"strip8x4": (8, 4), "strip8x1": (8, 1), "strip4x4": (4, 4), "strip5x1": (5, 1)}
     shy = {"stripyx8x4": (8, 4), "stripyx4x8": (4, 8), "stripyx8x8": (8, 8), "stripyx2x8": (2, 8),
            "stripyx2x16": (2, 16)}

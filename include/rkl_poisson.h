@@ -316,7 +316,8 @@ typedef struct {
     int variant;         /* see above                                        */
     int target;          /* workgroups aimed for (>= 1)                      */
     double us;           /* mean launch time in microseconds (rkl_autotune), */
-                         /* or 0 in an entry set by hand                     */
+                         /* 0 in an entry set by hand; installing one below  */
+                         /* 0 restores the level's built-in choice           */
 } rkl_tune_entry;
 
 /* Install n entries (host array).  RKL_EINVAL for a malformed entry, a
@@ -325,10 +326,14 @@ typedef struct {
 rkl_status rkl_tune_set(const rkl_tune_entry *entries, int n);
 /* Drop every tile entry and every stage-count entry. */
 rkl_status rkl_tune_clear(void);
-/* The choice recorded for a level: its entry, or the built-in base choice, whose
- * strip shape and chunk length a launch on a level without an entry fits to the
- * level's size and the device (variant 0 if no fused tau-step applies). */
+/* The choice recorded for a level (variant 0 if no fused tau-step applies): its
+ * entry as installed, or, with us = -1, the built-in base choice, whose strip shape
+ * and chunk length a launch fits to the level's size (rkl_tune_launched). */
 rkl_status rkl_tune_get(const rkl_grid *level, int s, int prec, rkl_tune_entry *out);
+/* The choice that a single solve's tau-step on a level runs: its entry, or, with us
+ * = -1, the strip shape and workgroup count fitted to a level without one.
+ * (Installing what either query returns changes nothing.) */
+rkl_status rkl_tune_launched(const rkl_grid *level, int s, int prec, rkl_tune_entry *out);
 /*
  * Time every variant and target on one level shape: reps launches each on
  * library-allocated scratch (freed before return), HIP events on hip_stream.

@@ -67,7 +67,7 @@ class c_tune(ctypes.Structure):
 
 EXPORTS = ("rkl_default_opts", "rkl_poisson_solve", "mg_vcycle", "rkl_smooth", "rkl_residual",
            "rkl_restrict", "rkl_prolong_add", "rkl_coarse_solve", "rkl_poisson_solve_batched",
-           "rkl_tau_step_launches", "rkl_tune_set", "rkl_tune_clear", "rkl_tune_get", "rkl_autotune",
+           "rkl_tau_step_launches", "rkl_tune_set", "rkl_tune_clear", "rkl_tune_get", "rkl_tune_launched", "rkl_autotune",
            "rkl_tune_set_s", "rkl_level_shapes", "rkl_variant_name", "rkl_gsrb_smooth", "rkl_default_relax_opts",
            "rkl_relax_solve", "rkl_gradient", "rkl_last_error", "rkl_release_all", "rkl_smooth_f32",
            "mg_vcycle_f32", "rkl_residual_f32", "rkl_restrict_f32", "rkl_prolong_add_f32", "rkl_coarse_solve_f32",
@@ -121,6 +121,7 @@ def load_library(path: str = LIB_PATH):
     lib.rkl_tune_set.argtypes = [pt, ctypes.c_int]
     lib.rkl_tune_clear.argtypes = []
     lib.rkl_tune_get.argtypes = [pg, ctypes.c_int, ctypes.c_int, pt]
+    lib.rkl_tune_launched.argtypes = [pg, ctypes.c_int, ctypes.c_int, pt]
     lib.rkl_autotune.argtypes = [pg, ctypes.c_int, ctypes.c_int, ctypes.c_int, pt, ctypes.c_int,
                                  ctypes.POINTER(ctypes.c_int), P]
     lib.rkl_tune_set_s.argtypes = [pg, ctypes.c_int, ctypes.c_int]
@@ -527,7 +528,7 @@ def kernel_info(shape, s, bc="periodic", prec="fp64", h=1.0):
     tname = "double" if prec == "fp64" else "float"
     if launches == 1:
         words = 3.0
-        v = tune_get(shape, s, bc, prec, h)
+        v = tune_launched(shape, s, bc, prec, h)
         name = {"zq64x32": f"k_tau_zq<{tname}, {s}, 64, 32>", "zq64x16": f"k_tau_zq<{tname}, {s}, 64, 16>",
                 "ring64x4": f"k_fused_tau<{tname}, {s}, 64, 4>", "strip8x4": f"k_tau_strip<{tname}, {s}, 8, 4>",
                 "strip8x1": f"k_tau_strip<{tname}, {s}, 8, 1>", "strip4x4": f"k_tau_strip<{tname}, {s}, 4, 4>",
@@ -565,8 +566,8 @@ def _entry_c(d):
 
 
 def tune_set(entries):
-    """Install tile choices (dicts as returned by autotune_level / tune_get).
-    One without a time ("us" absent or 0) also holds the level's V-cycle strokes
+    """Install tile choices (dicts as returned by autotune_level, tune_get or
+    tune_launched; "us" below 0 restores the built-in choice).  One without a time ("us" absent or 0) also holds the level's V-cycle strokes
     to its strips, where small and two-dimensional levels otherwise take one
     launch per stroke."""
     lib = load_library()
@@ -579,11 +580,22 @@ def tune_clear():
 
 
 def tune_get(shape, s, bc="periodic", prec="fp64", h=1.0):
-    """The tile choice in effect for a level of shape (nz, ny, nx) (or a 2-D
-    (ny, nx) level; h = (hx, hy) marks a (1, ny, nx) shape as 2-D too)."""
-    lib = load_library()
+    """The tile choice recorded for a level of shape (nz, ny, nx) (or a 2-D
+    (ny, nx) level; h = (hx, hy) marks a (1, ny, nx) shape as 2-D too): its entry,
+    or the built-in base choice ("us" -1), whose strip shape and chunk length a
+    launch fits to the level's size (tune_launched)."""
+    return _tune_query("rkl_tune_get", shape, s, bc, prec, h)
+
+
+def tune_launched(shape, s, bc="periodic", prec="fp64", h=1.0):
+    """The tile choice that runs on a level: its entry, or the strip shape and
+    workgroup count fitted to a level without one."""
+    return _tune_query("rkl_tune_launched", shape, s, bc, prec, h)
+
+
+def _tune_query(name, shape, s, bc, prec, h):
     out = c_tune()
-    _check(lib.rkl_tune_get(ctypes.byref(_grid(shape, h, bc)), int(s), PREC[prec], ctypes.byref(out)))
+    _check(getattr(load_library(), name)(ctypes.byref(_grid(shape, h, bc)), int(s), PREC[prec], ctypes.byref(out)))
     return _entry_dict(out)
 
 

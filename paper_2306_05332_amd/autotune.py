@@ -43,7 +43,7 @@ def tune_levels(shapes, s_list=(2,), bcs=("periodic",), precs=("fp64", "mixed"),
                         seen.add(key)
                         _lib.tune_set([{"nx": lv[2], "ny": lv[1], "nz": lv[0], "bc": bc, "prec": prec, "s": s,
                                         "variant": 0, "target": 0}])
-                        heur = _lib.tune_get(lv, s, bc, prec, h)
+                        heur = _lib.tune_launched(lv, s, bc, prec, h)
                         res = _lib.autotune_level(lv, s, bc, prec, reps, h)
                         best = dict(res[0])
                         hv = [r["us"] for r in res if r["variant"] == heur["variant"] and r["target"] == heur["target"]]

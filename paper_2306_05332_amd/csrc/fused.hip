@@ -612,16 +612,20 @@ struct TuneKey {
     return std::tie(nx, ny, nz, periodic, dbl, s) < std::tie(o.nx, o.ny, o.nz, o.periodic, o.dbl, o.s);
   }
 };
+struct TuneValue {
+  FusedChoice c;
+  double us;
+};
 std::mutex g_tune_mu;
-std::map<TuneKey, FusedChoice> g_tune;
+std::map<TuneKey, TuneValue> g_tune;
 int g_tune_gen = 0;
 }  // namespace
 
-void tune_install(int nx, int ny, int nz, int periodic, int dbl, int s, FusedChoice c) {
+void tune_install(int nx, int ny, int nz, int periodic, int dbl, int s, FusedChoice c, double us) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   const TuneKey k{nx, ny, nz, periodic ? 1 : 0, dbl ? 1 : 0, s};
   if (c.variant == FV_HEUR) g_tune.erase(k);
-  else g_tune[k] = c;
+  else g_tune[k] = TuneValue{c, us};
   ++g_tune_gen;
 }
 
@@ -711,26 +715,31 @@ static FusedChoice for_batch(FusedChoice c, int nb) {
 
 // the level's entry, if it has one that fits
 template <typename T>
-static bool fused_entry(const LevelView<T>& L, int s, FusedChoice& c) {
+static bool fused_entry(const LevelView<T>& L, int s, FusedChoice& c, double* us = nullptr) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tune.find(TuneKey{L.nx, L.ny, L.nz, L.periodic ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s});
-  if (it == g_tune.end() || !fused_variant_ok<T>(it->second.variant, s) || !variant_fits(L, it->second.variant))
+  if (it == g_tune.end() || !fused_variant_ok<T>(it->second.c.variant, s) ||
+      !variant_fits(L, it->second.c.variant))
     return false;
-  c = it->second;
+  c = it->second.c;
+  if (us != nullptr) *us = it->second.us;
   return true;
 }
 
 template <typename T>
-FusedChoice fused_recorded(const LevelView<T>& L, int s) {
+FusedChoice fused_recorded(const LevelView<T>& L, int s, double* us) {
   FusedChoice c;
-  return fused_entry<T>(L, s, c) ? c : fused_base<T>(L, s);
+  if (fused_entry<T>(L, s, c, us)) return c;
+  *us = -1.0;
+  return fused_base<T>(L, s);
 }
 
 template <typename T>
 bool fused_pinned(const LevelView<T>& L, int s) {
   FusedChoice c;
-  if (fused_entry<T>(L, s, c) && c.pinned) return true;
-  return level_is_2d(L) && fused_entry<T>(L, 2 * s, c) && c.pinned;
+  double us;
+  if (fused_entry<T>(L, s, c, &us) && us == 0.0) return true;
+  return level_is_2d(L) && fused_entry<T>(L, 2 * s, c, &us) && us == 0.0;
 }
 
 template <typename T>
@@ -1086,7 +1095,7 @@ const char* fused_variant_name(int variant) {
   template bool fused_tau_supported<T>(const LevelView<T>&, int);                                                 \
   template bool fused_variant_ok<T>(int, int);                                                                    \
   template FusedChoice fused_choice<T>(const LevelView<T>&, int, int);                                            \
-  template FusedChoice fused_recorded<T>(const LevelView<T>&, int);                                               \
+  template FusedChoice fused_recorded<T>(const LevelView<T>&, int, double*);                                      \
   template bool fused_pinned<T>(const LevelView<T>&, int);                                                        \
   template size_t fused_tau_blocks<T>(const LevelView<T>&, int, int);                                             \
   template size_t fused_tau_blocks_as<T>(const LevelView<T>&, FusedChoice, int);                                  \

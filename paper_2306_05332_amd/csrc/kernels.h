@@ -185,17 +185,18 @@ inline bool level_is_2d(const LevelView<T>& L) { return L.nz == 1 && L.ihz2 == (
 struct FusedChoice {
   int variant;
   int target;
-  bool pinned = false;  // an entry set by hand (no time): the level's strokes stay with the strips
 };
 template <typename T>
 bool fused_variant_ok(int variant, int s);
 template <typename T>
 FusedChoice fused_choice(const LevelView<T>& L, int s, int nb = 1);  // nb: members of the batch
-// the timed entry, else the built-in base choice (what rkl_tune_get reports)
+// the level's entry, else the built-in base choice (what rkl_tune_get reports);
+// us: the entry's time, or -1 for the base choice
 template <typename T>
-FusedChoice fused_recorded(const LevelView<T>& L, int s);
-// whether the level has a pinned entry for s stages (two-dimensional levels: or
-// for a pair of such tau-steps)
+FusedChoice fused_recorded(const LevelView<T>& L, int s, double* us);
+// whether the level has an entry without a time (one set by hand) for s stages
+// (two-dimensional levels: or for a pair of such tau-steps): its strokes then stay
+// with the strips
 template <typename T>
 bool fused_pinned(const LevelView<T>& L, int s);
 template <typename T>
@@ -292,7 +293,7 @@ void launch_gradient(int nx, int ny, int nz, double hx, double hy, double hz, in
 // max |M u - b| over the level: per-block maxima in part, reduced into out[0]
 template <typename T>
 void launch_resid_absmax(const LevelView<T>& L, const T* u, const T* b, double* part, double* out, hipStream_t st);
-void tune_install(int nx, int ny, int nz, int periodic, int dbl, int s, FusedChoice c);  // FV_HEUR erases
+void tune_install(int nx, int ny, int nz, int periodic, int dbl, int s, FusedChoice c, double us);  // FV_HEUR erases
 void tune_clear();
 int tune_generation();
 const char* fused_variant_name(int variant);

@@ -105,9 +105,35 @@ int autotune_level(const rkl_grid& g, int s, int prec, int reps, rkl_tune_entry*
     }
   }
   std::sort(all.begin(), all.end(), [](const rkl_tune_entry& a, const rkl_tune_entry& b) { return a.us < b.us; });
-  tune_install(g.nx, g.ny, g.nz, per ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s, FusedChoice{all[0].variant, all[0].target});
+  tune_install(g.nx, g.ny, g.nz, per ? 1 : 0, sizeof(T) == 8 ? 1 : 0, s, FusedChoice{all[0].variant, all[0].target},
+               all[0].us);
   for (int q = 0; q < (int)all.size() && q < cap; ++q) res[q] = all[q];
   return (int)all.size();
+}
+
+// The choice recorded for a level, or the one launched on it.
+void tune_query(const rkl_grid* level, int s, int prec, rkl_tune_entry* out, bool launched) {
+  validate_grid(level, nullptr);
+  if (!out) fail(RKL_EINVAL, "out must be non-NULL");
+  if (s < 1 || s > 64) fail(RKL_EINVAL, "s must be in [1, 64]");
+  const Lev Lv = build_levels(*level, INT_MAX, s, 0.9)[0];
+  const bool per = level->bc == RKL_BC_PERIODIC;
+  FusedChoice c{FV_HEUR, 0};
+  double us = -1.0;
+  auto ask = [&](auto tag) {
+    using T = decltype(tag);
+    const LevelView<T> V = view<T>(Lv, per, nullptr);
+    if (!fused_tau_supported<T>(V, s)) return;
+    c = fused_recorded<T>(V, s, &us);
+    if (!launched || us >= 0.0) return;
+    c = fused_choice<T>(V, s);
+    // the grid it comes to, which is one of those that rkl_autotune times
+    if (fused_chunk_blocks<T>(V, c.variant, s) > 0 && !level_is_2d(V)) c.target = (int)fused_tau_blocks_as<T>(V, c, s);
+  };
+  if (prec == RKL_FP64) ask(0.0);
+  else if (prec == RKL_MIXED) ask(0.0f);
+  else fail(RKL_EINVAL, "unknown precision");
+  *out = rkl_tune_entry{level->nx, level->ny, level->nz, (int)level->bc, prec, s, c.variant, c.target, us};
 }
 
 }  // namespace rkl
@@ -132,7 +158,8 @@ rkl_status rkl_tune_set(const rkl_tune_entry* entries, int n) {
     }
     for (int q = 0; q < n; ++q) {
       const rkl_tune_entry& e = entries[q];
-      tune_install(e.nx, e.ny, e.nz, e.bc == RKL_BC_PERIODIC, e.prec == RKL_FP64, e.s, FusedChoice{e.variant, e.target, e.us == 0.0});
+      tune_install(e.nx, e.ny, e.nz, e.bc == RKL_BC_PERIODIC, e.prec == RKL_FP64, e.s,
+                   FusedChoice{e.us < 0.0 ? FV_HEUR : e.variant, e.target}, e.us);
     }
     return RKL_OK;
   });
@@ -149,22 +176,14 @@ rkl_status rkl_tune_clear(void) {
 
 rkl_status rkl_tune_get(const rkl_grid* level, int s, int prec, rkl_tune_entry* out) {
   return guarded([&]() -> rkl_status {
-    validate_grid(level, nullptr);
-    if (!out) fail(RKL_EINVAL, "out must be non-NULL");
-    if (s < 1 || s > 64) fail(RKL_EINVAL, "s must be in [1, 64]");
-    const Lev Lv = build_levels(*level, INT_MAX, s, 0.9)[0];
-    const bool per = level->bc == RKL_BC_PERIODIC;
-    FusedChoice c{FV_HEUR, 0};
-    if (prec == RKL_FP64) {
-      const LevelView<double> V = view<double>(Lv, per, nullptr);
-      if (fused_tau_supported<double>(V, s)) c = fused_recorded<double>(V, s);
-    } else if (prec == RKL_MIXED) {
-      const LevelView<float> V = view<float>(Lv, per, nullptr);
-      if (fused_tau_supported<float>(V, s)) c = fused_recorded<float>(V, s);
-    } else {
-      fail(RKL_EINVAL, "unknown precision");
-    }
-    *out = rkl_tune_entry{level->nx, level->ny, level->nz, (int)level->bc, prec, s, c.variant, c.target, 0.0};
+    tune_query(level, s, prec, out, false);
+    return RKL_OK;
+  });
+}
+
+rkl_status rkl_tune_launched(const rkl_grid* level, int s, int prec, rkl_tune_entry* out) {
+  return guarded([&]() -> rkl_status {
+    tune_query(level, s, prec, out, true);
     return RKL_OK;
   });
 }

@@ -77,3 +77,24 @@ def test_forced_two_dimensional_variant_keeps_the_separate_passes(prec, dtype):
     # the passes round once more in between than a window does
     eps = 1e-13 if prec == "fp64" else 1e-5
     assert float((got - free).abs().max()) <= eps * float(free.abs().max())
+
+
+@pytest.mark.parametrize("bc", ["periodic", "dirichlet"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape", [(100, 100, 100), (72, 130, 160), (300, 300, 300)])
+def test_the_query_names_the_kernel_that_runs(shape, prec, bc):
+    """Levels without an entry: the tau-step that kernel_info names is the one a
+    sweep launches, also after the recorded choice was read and installed again."""
+    import paper_2306_05332_amd as R
+    R.tune_clear()
+    f = torch.ones(shape, dtype=torch.float64 if prec == "fp64" else torch.float32, device="cuda")
+    phi = torch.zeros_like(f)
+
+    def sweep():
+        return [n for n in _trace(lambda: R.smooth(f, phi, 1.0, bc, s=2, n_steps=2)) if "k_tau" in n]
+
+    want = R.kernel_info(shape, 2, bc, prec)["kernel"].rstrip(">") + ","
+    names = sweep()
+    assert len(names) == 2 and all(want in n for n in names), (want, names)
+    R.tune_set([R.tune_get(shape, 2, bc, prec)])
+    assert sweep() == names
