@@ -61,7 +61,7 @@ __global__ __launch_bounds__(FNT) void k_fused_tau(LevelView<T> L, const T* __re
   const bool per = L.periodic != 0;
   const size_t sxy = (size_t)nx * ny;
 
-  const int bid = xcd_tile(blockIdx.x, nblk);
+  const int bid = (nblk & 7) == 0 ? xcd_tile(blockIdx.x, nblk) : blockIdx.x;  // (see xcd_tile)
   const int tx = bid % gx_tiles;
   const int ty = (bid / gx_tiles) % gy_tiles;
   const int tz = bid / (gx_tiles * gy_tiles);
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(NT) void k_tau_zq(LevelView<T> L, const T* __restri
   const int nx = L.nx, ny = L.ny, nz = L.nz;
   const bool per = L.periodic != 0;
   const size_t sxy = (size_t)nx * ny;
-  const int bid = xcd_tile(blockIdx.x, nblk);
+  const int bid = (nblk & 7) == 0 ? xcd_tile(blockIdx.x, nblk) : blockIdx.x;  // (see xcd_tile)
   const int tx = bid % gx_tiles;
   const int ty = (bid / gx_tiles) % gy_tiles;
   const int tz = bid / (gx_tiles * gy_tiles);
