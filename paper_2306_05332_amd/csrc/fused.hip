@@ -672,7 +672,8 @@ FusedChoice fused_base(const LevelView<T>& L, int s) {
 // What such a level runs: where the base choice is a strip, the strip shape and
 // chunk length that suit its size and the device.  Lines drawn from timing
 // every strip shape and chunk length on 25 shapes from 20 x 24 x 28 to 320 x
-// 384 x 384 (s = 2); means of the gain over the base choice:
+// 384 x 384 (s = 2); means of the gain over the base choice, which float64 steps of
+// one stage keep (fitted: 0.6 % on average over 13 shapes, 256^3 87 -> 92 us):
 //  * float64, periodic: stacked two-row strips, two workgroups per CU, from
 //    1.25 million cells (256^3 101 -> 82 us, 190 x 256 x 384 117 -> 96,
 //    160^3 25 -> 23), five-row one-wavefront strips, one per SIMD, below (100^3
@@ -686,12 +687,12 @@ FusedChoice fused_base(const LevelView<T>& L, int s) {
 //    periodic, 1.01 x Dirichlet.
 template <typename T>
 FusedChoice fused_heuristic(const LevelView<T>& L, int s) {
-  if (!level_is_2d(L) && fused_variant_ok<T>(FV_STRIP_4x4, s)) {
+  if (!level_is_2d(L) && fused_variant_ok<T>(FV_STRIP_4x4, s) && (sizeof(T) == 4 || s == 2)) {
     const size_t n = (size_t)L.nx * L.ny * L.nz;
     const bool big = 3 * sizeof(T) * n > ((size_t)256 << 20);
     auto fill = [&](int variant, int slots) { return strip_filling(variant, s, L.nx, L.ny, L.nz, slots); };
     if (sizeof(T) == 8) {
-      if (s <= 2 && (big || (L.periodic && n >= 1250000))) return fill(FV_STRIPYX_2x8, 512);
+      if (big || (L.periodic && n >= 1250000)) return fill(FV_STRIPYX_2x8, 512);
       return L.periodic ? fill(FV_STRIP_5x1, 1024) : fill(FV_STRIP_4x4, 512);
     }
     if (big) return L.periodic ? fill(FV_STRIPYX_8x4, 512) : fill(FV_STRIPYX_4x8, 512);

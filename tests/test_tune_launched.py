@@ -54,3 +54,12 @@ def test_launched_strips_state_their_workgroups(L):
     assert e["target"] % per == 0
     chunks = e["target"] // per
     assert any(chunks == -(-300 // zc) for zc in range(1, 65))
+
+
+@pytest.mark.parametrize("bc", ["periodic", "dirichlet"])
+@pytest.mark.parametrize("shape", [(300, 300, 300), (160, 160, 160), (40, 40, 40)])
+def test_float64_steps_of_one_stage_keep_the_base_choice(L, shape, bc):
+    """The fitted shapes were timed on two stages; with one they lose as often as
+    they win."""
+    base, got = L.tune_get(shape, 1, bc, "fp64"), L.tune_launched(shape, 1, bc, "fp64")
+    assert got["variant"] == base["variant"]
