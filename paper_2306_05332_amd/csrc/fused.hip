@@ -707,10 +707,24 @@ FusedChoice fused_heuristic(const LevelView<T>& L, int s) {
 // level 0: fused restriction 164 us, prolongation 159, tau-step 113, against
 // 114 / 108 / 85 us on the same number of cells at 256^3; forward + adjoint
 // 17.2 -> 14.3 ms with the targets shared, 48 mixed boxes of 32^3 to 128^3 8.5
-// -> 7.2 ms).  The cut does not enter the arithmetic: a member's answer is its
-// single solve's.
+// -> 7.2 ms).  A level whose own count leaves most of the device idle (strips of
+// fewer than one and a half wavefronts per SIMD) is not cut below two per SIMD
+// over all members: dividing its count made the members march where one of them
+// alone is cut to single planes (separate passes, 32 members of 24^3 float64 1491 ->
+// 1096 us, 64 of 16^3 float32 Dirichlet 1521 -> 1218, 16 of 64^3 2994 -> 2572; 2.4 %
+// on average over 416 batches, none slower).  The cut does not enter the
+// arithmetic: a member's answer is its single solve's, its residual norms to
+// rounding, as their partial sums are cut likewise.
 static FusedChoice for_batch(FusedChoice c, int nb) {
-  c.target = std::max(1, c.target / std::max(1, nb));
+  if (nb <= 1) return c;
+  constexpr int SIMDS = 1024;
+  int share = c.target / nb;
+  if (is_strip(c.variant) || variant_is_2d(c.variant)) {
+    int R, waves = 1;
+    if (is_strip(c.variant)) strip_shape(c.variant, R, waves);
+    if (2ll * c.target * waves < 3 * SIMDS) share = std::max(share, std::min(c.target, 2 * SIMDS / waves / nb));
+  }
+  c.target = std::max(1, share);
   return c;
 }
 
