@@ -95,7 +95,8 @@ typedef struct {
     double coarse_tol;   /* coarsest solve: stop at ||M u - b|| <= coarse_tol ||b||; 0 picks
                             1e-13 (float64) or 1e-6 (float32), which V-cycles then reach by a
                             direct solve of the coarsest system (fast diagonalisation) when the
-                            accelerated RKL steps would reach it within coarse_max_steps         */
+                            accelerated RKL steps would reach it within coarse_max_steps and no
+                            axis of the coarsest level has more than 512 cells                   */
     int coarse_max_steps;/* coarsest solve: cap on tau-steps (default 200)                      */
     int smoother;        /* rkl_smoother: relaxation of the V-cycle above the coarsest level    */
                          /* (default RKL_SMOOTH_RKL)                                            */
@@ -255,8 +256,11 @@ rkl_status rkl_coarse_solve_f32(const rkl_grid *grid, const rkl_opts *opts, cons
  * not fit the device's free memory, is solved member by member with the
  * single-solve path.  Returns the first non-OK member status in class order
  * (each member's own outcome is in stats[i]); phi of periodic members is
- * mean-free.  Calls on one process are serialised.  Buffers persist until
- * rkl_release_all.
+ * mean-free.  A member's phi is what its single solve returns; its residual
+ * history agrees to rounding, since the partial sums behind the norms are cut by
+ * the member count.  Calls on one process are serialised.  Buffers persist until
+ * rkl_release_all, those of classes with a coarsest level of more than 256 cells
+ * within 2^26 level-0 cells in all.
  */
 rkl_status rkl_poisson_solve_batched(const rkl_grid *grids, int nbatch, const rkl_opts *opts,
                                      const double *const *rho, double *const *phi,

@@ -152,7 +152,7 @@ void class_iteration(ClassPlan& C, Hier<T>& H, const rkl_opts& o, hipStream_t st
   T* cur = H.u[0];
   T* alt = H.t[0];
   const Batch b0{nb, (long long)F.n, 0, CONV_INTS, ps};
-  const VBatch vb{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw};
+  const VBatch vb{nb, CONV_INTS, ps, C.part, C.dirw};
   const int down = level0_down<T>(P, H, nullptr, H.b[0], cur, o, nullptr, nullptr, stop, st, vb);
   if (down == 0) launch_check(chk, st, nb);
   int pre_done = 0;
@@ -184,7 +184,7 @@ void class_iteration_direct(ClassPlan& C, const rkl_opts& o, hipStream_t st, int
   const bool pair0 = o.n_pre >= 2 && pair_ok<double>(V0, o.s, gs);
   const Batch b0{nb, (long long)F.n, 0, CONV_INTS, ps};
   double *cur = bufs[(ia + 1) % 3], *alt = bufs[(ia + 2) % 3];
-  const VBatch vb{nb, CONV_INTS, ps, C.dsum, C.part, C.dirw};
+  const VBatch vb{nb, CONV_INTS, ps, C.part, C.dirw};
   const int down = level0_down<double>(P, H, bufs[ia], C.f0, cur, o, C.part, nullptr, stop, st, vb);
   int nblk = down;
   if (down == 0) {

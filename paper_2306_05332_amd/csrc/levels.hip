@@ -85,7 +85,7 @@ void vcycle_impl(Plan& P, const rkl_opts& o, const T* b, T* phi, double* rel_out
   T* home = nullptr;
   int pre_done = 0;
   const int down = level0_down<T>(P, H, phi, b, alt, o, nullptr, P.periodic ? P.part : nullptr, nullptr, st,
-                                  VBatch{1, 0, 0, P.dscal});
+                                  VBatch{});
   if (down > 0) {
     std::swap(cur, alt);
     pre_done = o.n_pre;
@@ -95,7 +95,7 @@ void vcycle_impl(Plan& P, const rkl_opts& o, const T* b, T* phi, double* rel_out
     pre_done = 1;
     home = phi;
   }
-  vcycle_from<T>(P, H, cur, alt, b, nullptr, pre_done, o, nullptr, st, VBatch{1, 0, 0, P.dscal}, false, home,
+  vcycle_from<T>(P, H, cur, alt, b, nullptr, pre_done, o, nullptr, st, VBatch{}, false, home,
                   down);
   copy_back<T>(phi, cur, P.lv[0].n, st);
   if (rel_out) {

@@ -262,7 +262,7 @@ rkl_status solve_fp64(Plan& P, const rkl_opts& o, const double* rho, const doubl
       double* a = bufs[ia];
       double *cur, *alt;
       int pre_done;
-      const VBatch vb{1, 0, 0, P.dscal};
+      const VBatch vb{};
       // small grids: the whole downstroke, with the residual norm of the start
       // state (not from the zero iterate, whose residual is f)
       const int down =
@@ -367,12 +367,13 @@ rkl_status solve_mixed(Plan& P, const rkl_opts& o, const double* rho, const doub
       const CheckArgs chk{P.part, nblk, 2, Res0Sqrt::ptr(P), o.tol, o.max_cycles, (double)F.n, P.dconv, 0};
       check_launch();
       // periodic: the defect of the mean-free f sums to zero up to rounding
-      // (the periodic M sums to zero); the rounding-level mean that the
-      // restriction carries is dropped on level 1, so level 0 needs no pass
-      // one float32 V-cycle on M e = r from e = 0 (homogeneous level-0 ghosts)
+      // (the periodic M sums to zero), so level 0 needs no pass; the
+      // rounding-level mean that the restrictions carry is dropped in the tail or
+      // by the direct coarsest solve.
+      // One float32 V-cycle on M e = r from e = 0 (homogeneous level-0 ghosts)
       float* cur = P.h32.u[0];
       float* alt = P.h32.t[0];
-      const VBatch vb{1, 0, 0, P.dscal};
+      const VBatch vb{};
       const int down =
           level0_down<float>(P, P.h32, nullptr, P.h32.b[0], cur, o, nullptr, nullptr, stop, st, vb);  // small grids
       if (down == 0) launch_check(chk, st);

@@ -453,14 +453,12 @@ void coarse_solve(Plan& P, Hier<T>& H, int l, const rkl_opts& o, const int* stop
   accel_multi<T>(P, V, H.u[l], H.t[l], H.b[l], tol, bn, o.coarse_max_steps, P.periodic, st, nullptr);
 }
 
-// The V-cycle of Sec. 2.1 on M_0 u = b0 below the first level-0 relaxation.
-// On entry cur0 holds the iterate after `pre_done` level-0 relaxations
-// (alt0 is its alternate buffer); on exit cur0 holds the cycle's result.
-// faces0: level-0 Dirichlet data (float64 path only) or nullptr.
 // Whether the coarsest level is solved directly: the caller left the
 // tolerance at its default and the iteration would reach it within the step
-// cap, so both give the solution to that tolerance or better.  A tolerance or
-// a cap of the caller's own runs the accelerated RKL iteration as asked.
+// cap (accel_steps.h), so both give the solution to that tolerance or better, and
+// no axis of the level is longer than the direct solve takes (direct_axes_ok).
+// A tolerance or a cap of the caller's own runs the accelerated RKL iteration as
+// asked.
 template <typename T>
 bool direct_coarse(const Plan& P, const rkl_opts& o) {
   const int steps = sizeof(T) == 8 ? P.steps64 : P.steps32;
@@ -474,13 +472,11 @@ int tail_level(const Plan& P, bool direct) {
 }
 
 // Batch geometry of the V-cycle: nb members whose level-l arrays are nb
-// contiguous blocks of n_l cells; stop flags and partial sums strided per
-// member; dsum: two doubles per member of scratch for periodic means.
+// contiguous blocks of n_l cells; stop flags and partial sums strided per member.
 struct VBatch {
   int nb = 1;
   int stop_stride = 0;
   int part_stride = 0;
-  double* dsum = nullptr;
   double* part = nullptr;  // nullptr: the plan's own buffer
   double* dirw = nullptr;  // direct coarsest solve's scratch (nullptr: the plan's own)
 };
@@ -501,6 +497,10 @@ int level0_down(Plan& P, Hier<T>& H, const T* u0, const T* b, T* u, const rkl_op
   return n;
 }
 
+// The V-cycle of Sec. 2.1 on M_0 u = b0 below the first level-0 relaxation.
+// On entry cur0 holds the iterate after `pre_done` level-0 relaxations
+// (alt0 is its alternate buffer); on exit cur0 holds the cycle's result.
+// faces0: level-0 Dirichlet data (float64 path only) or nullptr.
 //
 // Periodic compatibility (Sec. 2.3): the restricted residual of a mean-free
 // right-hand side is mean-free up to rounding, since the periodic M sums to

@@ -64,8 +64,14 @@ static int launch_rs_k(const LevelView<T>& L, const T* u, const T* b, T* out, T*
   // One wave of resident workgroups, or, where that takes chunks of more than 64
   // planes, short chunks in many waves: a wave and a part of one leaves CUs idle
   // at the end, and long chunks spread the accesses.  A cycle's time with chunks
-  // of 64, 16 and 40 planes: float32 448^3 1263, 1120, 1161 us, 512^3 1727, 1631
-  // and 1710; float64 400 x 480 x 360 1633, 1631 and 1575.
+  // of 64 and 16 planes, float32: 384^3 periodic 704 and 684 us, Dirichlet 862 and
+  // 846; 576 x 320 x 448 1104 and 1005, 1230 and 1140; 448^3 1186 and 1077, 1357 and
+  // 1233; 512^3 1644 and 1560, 1819 and 1667; 288^3 to 384 x 384 x 320 within 2 %.
+  // Float64 gains less from short chunks, as it is bound by bytes: of 64, 40 and 24
+  // planes, 288^3 643, 594 and 594 us (Dirichlet 732, 680 and 653), 400^3 1438, 1413
+  // and 1463, 448^3 2016, 2012 and 2046, 512^3 2729, 2729 and 2759, 384 x 384 x 320
+  // 1061, 1103 and 1107: 40 is 0.9 % ahead of 64 over 11 shapes and both boundary
+  // types, and loses up to 4 % where 64 happens to fill whole waves.
   const StripGrid g = strip_grid_rs(S, R, WY, L.nx, L.ny, L.nz,
                                     std::max(1, resident_wgs(kern, 64 * WY, slots) / bt.nb), sizeof(T) == 4 ? 16 : 40);
   hipLaunchKernelGGL(kern, dim3(g.nblk, bt.nb), dim3(64 * WY), 0, st, L, u, b, out, bc, fc, g.zc, g.gx, g.gy, g.nblk,
