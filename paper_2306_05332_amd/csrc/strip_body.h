@@ -408,11 +408,21 @@ __device__ __forceinline__ void tau_strip_body(LevelView<T> L, const T* __restri
         // compiler from moving the reads above the wait)
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        T P[NC], N[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          X[c] = (T)0;
-          if (cneed(c)) X[c] = (sz * csg[c]) * fma3((T)cdma[w][c][cofp], sxn * (T)cdma[w][c][cofn]);
+          P[c] = N[c] = (T)0;
+          if (cneed(c)) {
+            P[c] = (T)cdma[w][c][cofp];
+            N[c] = (T)cdma[w][c][cofn];
+          }
         }
+        // lgkmcnt(0): the reads are complete before direct loads of a later plane
+        // may be issued into the same slots (nothing orders the two in LDS)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) X[c] = cneed(c) ? (sz * csg[c]) * fma3(P[c], sxn * N[c]) : (T)0;
       } else {
 #pragma unroll
         for (int c = 0; c < NC; ++c) X[c] = (sz * csg[c]) * fma3(C[c][0], sxn * C[c][1]);
